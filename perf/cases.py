@@ -34,8 +34,8 @@ def listed():
         # A small cell at the Gamma point, odd order, with the energy-density matrix that forces need.
         dict(name="gamma333", kind="solve", n=333, kT=0.02, forces=True),
         # A 16-atom cell on a 2x2x2 k mesh, second and later self-consistent cycles: cached overlap,
-        # occupied window only, the launch sequence replayed as a graph.
-        dict(name="kscf8x208", kind="scf", n=208, batch=8, complex=True, kT=0.02, graph=True),
+        # occupied window only.
+        dict(name="kscf8x208", kind="scf", n=208, batch=8, complex=True, kT=0.02),
         # A 20-atom noncollinear cell at a general k-point (complex overlap), order 520.
         dict(name="spinor520", kind="solve", n=260, spinor=True, complex=True),
         # One k-point by the Loewdin route, the one the paper takes, 100 atoms.
@@ -81,8 +81,6 @@ def draw(rng):
             case["mixed"] = True
         elif rng.random() < 0.2:
             case["lowdin"] = True
-        elif case["kind"] == "scf" and case["n"] <= 600 and rng.random() < 0.5:
-            case["graph"] = True
         elif case["kind"] == "solve" and rng.random() < 0.4:
             case["forces"] = True
         if case.get("spinor") and "lowdin" not in case and rng.random() < 0.5:
@@ -258,11 +256,10 @@ def prepare(case, seed):
         st["grad_rho"] = torch.randn(H.shape, generator=g, dtype=H.dtype, device="cuda")
         st["grad_eband"] = torch.ones(1, dtype=torch.float64, device="cuda")
         return st
-    flags = (ks.KS_PLAN_LOWDIN if case.get("lowdin") else 0) | (ks.KS_PLAN_GRAPH if case.get("graph") else 0)
+    flags = (ks.KS_PLAN_LOWDIN if case.get("lowdin") else 0)
     flags |= ks.KS_PLAN_REAL_OVERLAP if case.get("real_overlap") else 0
-    st["stream"] = torch.cuda.Stream() if case.get("graph") else torch.cuda.current_stream()
     plan = st["plan"] = ks.Plan(n, batch=batch, complex=bool(case.get("complex")), noncollinear=bool(case.get("spinor")),
-                                precision=ks.KS_MIXED if case.get("mixed") else ks.KS_FP64, stream=st["stream"], flags=flags)
+                                precision=ks.KS_MIXED if case.get("mixed") else ks.KS_FP64, flags=flags)
     if kind == "bloch":
         g = torch.Generator(device="cuda").manual_seed(int(seed))
         st["HR"], st["SR"], st["R"], st["k"] = _real_space(g, case)
@@ -276,7 +273,6 @@ def prepare(case, seed):
         st["occ"], st["C"], st["rho"] = torch.empty_like(st["eps"]), torch.zeros_like(st["H"]), torch.empty_like(st["H"])
         st["mu"], st["eband"] = (torch.empty(1, dtype=torch.float64, device="cuda") for _ in range(2))
         # the first cycle of the loop: it leaves the overlap's factor in the plan
-        torch.cuda.synchronize()
         plan.gevd(st["H"], st["S"], st["eps"], st["C"], il=1, iu=_window(case))
         plan.check()
     return st
