@@ -59,6 +59,13 @@ int32_t ks_test_he2hb(int32_t dtype, int32_t n, void* A, const double* X, int32_
  * lets a test drive that failure path with ordinary inputs. */
 int32_t ks_test_set_iteration_caps(int32_t leaf_sweeps, int32_t secular_iters);
 
+/* Gangs of workgroups of the tridiagonalisation, for the solves that the calling
+ * thread enqueues from now on: 1 = those that take the whole GPU leave at once
+ * as if their workgroups had not become resident together, so that their form
+ * in memory does the columns; 2 = every gang does, so that one workgroup does
+ * them; 0 = none (the default).  Host-only. */
+int32_t ks_test_set_gang_leave(int32_t level);
+
 /* One v_mfma_f64_16x16x4_f64 where lane l feeds A[l%16][l/16] and B[l/16][l%16]
  * with A[i][0] = 100 i, A[i][1] = 1, B[0][j] = 1, B[1][j] = j (other k zero), so
  * D[i][j] = 100 i + j; out[lane * 4 + r] = accumulator register r of each lane. */

@@ -225,6 +225,10 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
     size_t oPR = L.take(B * hPR * es), oPC = L.take(B * hPC * es);
     size_t oPV = L.take(B * hPV * 8);
     size_t oPQv = L.take(B * hPQv * es);
+    size_t hGx = 3 * (order <= 512 ? 512 : order <= 1024 ? 1024 : order <= 2048 ? 2048 : GANG_ORDER);  // exchange slots of a gang: products, raw rows
+    size_t oGx = L.take(2 * B * hGx * es), oGs = L.take(B * GANG_STATE * sizeof(int));
+    const size_t hGm = es == 16 ? gang_mem<cplx>((int)order, (int)B) : gang_mem<double>((int)order, (int)B);
+    const size_t oGm = L.take(B * hGm * es);
     // back-transform
     const size_t nblk_bt = order > 1 ? (order - 1 + bt - 1) / bt : 1;
     size_t oG = L.take(B * bt * bt * es), oT = L.take(B * nblk_bt * bt * bt * es);
@@ -343,6 +347,13 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
         h.VWlo = mixed ? (void*)(b + oVWl) : nullptr;
         h.WVlo = mixed ? (void*)(b + oWVl) : nullptr;
         h.prof = &p->prof;
+        h.gang.xp = (T*)(b + oGx);
+        h.gang.xr = h.gang.xp + B * hGx;
+        h.gang.state = (int*)(b + oGs);
+        h.gang.sxp = h.gang.sxr = (long)hGx;
+        h.gang.mem = hGm ? (T*)(b + oGm) : nullptr;
+        h.gang.smem = (long)hGm;
+        h.info = p->info;
     };
     if (mixed) {
         p->A32 = b + oA32;
@@ -435,6 +446,20 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
     t.d_leaf_hi = (int*)(b + oL2);
     set_dc_leaf(p, DC_LEAF);
     return total;
+}
+
+// Compute units that the stream may use (a stream made with a mask has fewer
+// than the device).
+int stream_cus(hipStream_t s, int ncu) {
+    uint32_t mask[32] = {};
+    if (!s) return ncu;
+    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return ncu;
+    }
+    int n = 0;
+    for (uint32_t m : mask) n += __builtin_popcount(m);
+    return n > 0 ? std::min(n, ncu) : ncu;
 }
 
 bool range_ok(const ks_plan* p, int il, int iu) { return il >= 1 && il <= iu && iu <= p->order; }
@@ -1013,14 +1038,15 @@ ks_status ks_plan_create(const ks_plan_desc* d, ks_plan** out) {
     }
     p->bytes = bytes;
     layout(d, p);
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) {
+        (void)hipFree(p->base);
+        delete p;
+        return KS_ERR_HIP;
+    }
+    p->hr.gang.ncu = p->hc.gang.ncu = stream_cus(p->s, ncu);
     if (d->flags & KS_PLAN_TWOSTAGE) {
-        int dev = 0, ncu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) {
-            (void)hipFree(p->base);
-            delete p;
-            return KS_ERR_HIP;
-        }
         p->bandr.ncu = p->bandc.ncu = ncu;
         // the panel factorisation's workgroups of one matrix must all be resident together
         if (cdiv(p->order, panel_rows(p->is_c)) > ncu) {

@@ -21,6 +21,8 @@
 //         w = tau (A v - V p - W q) + alpha v, and, inside the panel, the update
 //         of column k+1 with the panel's reflectors and its partial sums
 //         |x|^2, W^H x, V^H x for the next reflector.
+// Once the trailing matrix fits the registers of the compute units (or of some
+// of them, for a batch) ks_trdres.hip does the rest.
 // After the panel the lower triangle of the trailing matrix takes the rank-2NB
 // update A -= V W^H + W V^H as one MFMA GEMM with K = 2 NB.
 // The panel buffers are stored transposed (NB columns of length n each) so
@@ -697,12 +699,6 @@ __global__ void store_panel_kernel(int n, int k0, int jb, const T* VWt, long sVW
     Vall[(long)r * n + k0 + i] = r > k0 + i ? VWt[(long)i * n + r] : zero_<T>();
 }
 
-template <typename S>
-__global__ void last_diag_kernel(int n, const S* A, int lda, long sA, double* d) {
-    const int z = blockIdx.x;
-    d[(long)z * n + n - 1] = re_(A[z * sA + (long)(n - 1) * lda + n - 1]);
-}
-
 // Launch the symmetric product of column k with sch tiles per workgroup.  With
 // events (either may be null), the launch itself records them at the kernel's
 // start and end (so the sampled duration is the kernel's own, without the gap
@@ -769,7 +765,8 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
     TrdGroup<T, S> g[2];
     int ng = 1;
     g[0] = {s, batch, A, d, e, tau, Vall, w};
-    if (w.side && batch >= 2) {
+    const int mres = resident_order<T>(batch, w.gang.ncu);
+    if (w.side && batch >= 2 && n > mres) {
         const int B0 = (batch + 1) / 2;
         g[0].B = B0;
         HetrdWork<T> w1 = w;
@@ -790,7 +787,8 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
         (void)hipEventRecord(w.fork, s);
         (void)hipStreamWaitEvent(w.side, w.fork, 0);
     }
-    for (int k0 = 0; k0 < n - 1; k0 += nb) {
+    int k0 = 0;
+    for (; n - k0 > mres; k0 += nb) {
         int jb = min(nb, n - 1 - k0);
         for (int q = 0; q < ng; ++q) {
             TrdGroup<T, S>& G = g[q];
@@ -856,12 +854,13 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
             }
         }
     }
-    for (int q = 0; q < ng; ++q)
-        hipLaunchKernelGGL((last_diag_kernel<S>), dim3(g[q].B), dim3(1), 0, g[q].s, n, g[q].A, lda, sA, g[q].d);
     if (ng == 2) {
         (void)hipEventRecord(w.join, w.side);
         (void)hipStreamWaitEvent(s, w.join, 0);
     }
+    // the rest in registers, the whole batch in one launch: its gangs share the
+    // GPU (or follow each other) by themselves
+    hetrd_resident<T, S>(s, n, k0, A, lda, sA, batch, d, e, tau, Vall, w.gang, w.info);
 }
 
 

@@ -97,9 +97,26 @@ struct Prof {
 };
 constexpr int PROF_HEMV = 100;  // tag of the sampled kernel
 
+// Exchange buffers of a gang of workgroups that reduces the last columns of the
+// tridiagonalisation in registers (ks_trdres.hip), per matrix of a batch.
+constexpr int GANG_ORDER = 3072;    // largest order of a gang
+constexpr int GANG_STATE = 8;       // words of a matrix's state
+constexpr int GANG_CHIP_BATCH = 4;  // largest batch whose gangs take the whole chip in turn
+template <typename T>
+struct GangWork {
+    T* xp = nullptr;       // 3 slots of the products p = A v, one entry per row of a workgroup
+    T* xr = nullptr;       // 3 slots of the raw row that is the next column
+    int* state = nullptr;  // 8 words: the gang's state, workgroups that have arrived
+    T* mem = nullptr;      // order^2 entries, the rows of a whole-chip gang that could not gather (one matrix)
+    long sxp = 0, sxr = 0, smem = 0;  // strides between matrices
+    int ncu = 0;                      // compute units the plan's stream may use
+};
+
 template <typename T>
 struct HetrdWork {
     Prof* prof = nullptr;
+    GangWork<T> gang;
+    int* info = nullptr;
     T* VW;          // 2NB x n   V then W of the current panel, transposed
     T* WV;          // 2NB x n   conj(W) then conj(V), transposed
     T* x;           // n         updated column
@@ -252,6 +269,24 @@ void reduce_to_standard_real(hipStream_t s, int n, int nsp, int batch, const cpl
 template <typename T, typename S>
 void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, double* e, T* tau, T* Vall,
            HetrdWork<T>& w);
+
+// Largest trailing order that is reduced in registers (ks_trdres.hip), and the
+// columns from k0 on of every matrix of a batch reduced that way (A's trailing
+// rows and columns k0.. up to date in the lower triangle; d, e, tau and the
+// columns k0.. of Vall as from hetrd).  A gang whose workgroups do not become
+// resident together leaves its columns to slower kernels behind it; a wait
+// inside a gang that gives up records KS_ERR_NO_CONVERGENCE with detail -4.
+template <typename T>
+int resident_order(int batch, int ncu);
+template <typename T, typename S>
+void hetrd_resident(hipStream_t s, int n, int k0, S* A, int lda, long sA, int batch, double* d, double* e, T* tau,
+                    T* Vall, GangWork<T> gw, int* info);
+// Entries per matrix that GangWork::mem needs for a plan of this order.
+template <typename T>
+long gang_mem(int order, int batch);
+// Test hook, for the launches of the calling thread: 1 = the gangs that take the
+// whole chip leave at once, 2 = every gang does, 0 = none.
+void trd_set_leave(int level);
 
 // Tiles-per-workgroup candidates of the symmetric product for element type T,
 // and the time of `reps` launches of each at a few trailing sizes of an order-n
