@@ -227,8 +227,7 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
     size_t oPQv = L.take(B * hPQv * es);
     size_t hGx = 3 * (order <= 512 ? 512 : order <= 1024 ? 1024 : order <= 2048 ? 2048 : GANG_ORDER);  // exchange slots of a gang: products, raw rows
     size_t oGx = L.take(2 * B * hGx * es), oGs = L.take(B * GANG_STATE * sizeof(int));
-    const size_t hGm = es == 16 ? gang_mem<cplx>((int)order, (int)B) : gang_mem<double>((int)order, (int)B);
-    const size_t oGm = L.take(B * hGm * es);
+    size_t hGm = es == 16 ? gang_mem<cplx>((int)order, (int)B) : gang_mem<double>((int)order, (int)B);
     // back-transform
     const size_t nblk_bt = order > 1 ? (order - 1 + bt - 1) / bt : 1;
     size_t oG = L.take(B * bt * bt * es), oT = L.take(B * nblk_bt * bt * bt * es);
@@ -305,6 +304,7 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
     const size_t oFpart = lw ? L.take(B * ((order + 63) / 64) * 8) : 0;
     size_t total = L.off;
     if (!p) return total;
+    if ((es == 16 ? hGm * B > pel : hGm > 4 * order * order)) hGm = 0;  // (never, for the shapes there are)
     char* b = p->base;
     p->L = b + oL;
     if (lw) {
@@ -351,7 +351,9 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
         h.gang.xr = h.gang.xp + B * hGx;
         h.gang.state = (int*)(b + oGs);
         h.gang.sxp = h.gang.sxr = (long)hGx;
-        h.gang.mem = hGm ? (T*)(b + oGm) : nullptr;
+        // (free while the tridiagonalisation runs: 4 order^2 doubles of the
+        // divide and conquer, the split-K partial products for complex data)
+        h.gang.mem = hGm ? (T*)(b + (is_cplx<T>::value ? oSK : oZ)) : nullptr;
         h.gang.smem = (long)hGm;
         h.info = p->info;
     };
