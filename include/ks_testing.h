@@ -52,7 +52,7 @@ int32_t ks_test_hetrd2(int32_t dtype, int32_t n, void* A, double* d, double* e, 
 int32_t ks_test_he2hb(int32_t dtype, int32_t n, void* A, const double* X, int32_t ncols, void* Y, void* stream);
 
 /* Iteration caps of the divide-and-conquer eigensolver for every later call in
- * this process: Jacobi sweeps of the leaves (default 40) and iterations of the
+ * this process: QL sweeps per eigenvalue of the leaves (default 40) and iterations of the
  * secular-equation solver (default 120); a value <= 0 restores the default.
  * A step that reaches its cap records KS_ERR_NO_CONVERGENCE in the plan's info
  * word and finishes normally (its outputs are then undefined).  Host-only; it

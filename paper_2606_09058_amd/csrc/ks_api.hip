@@ -237,14 +237,14 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
     size_t pel = std::max<size_t>(16, (order + 255) / 256) * bt * order * B;
     size_t oSK = L.take(pel * es);
     // divide and conquer (per matrix of the batch)
-    size_t oDd[10];
-    for (int i = 0; i < 10; ++i) oDd[i] = L.take(B * order * 8);
+    size_t oDd[9];
+    for (int i = 0; i < 9; ++i) oDd[i] = L.take(B * order * 8);
     size_t oRcs = L.take(B * 2 * order * 8);
     size_t oDi[6];
     for (int i = 0; i < 6; ++i) oDi[i] = L.take(B * order * sizeof(int));
     size_t oRidx = L.take(B * 2 * order * sizeof(int));
     size_t oKK = L.take(B * maxm * sizeof(int)), oNR = L.take(B * maxm * sizeof(int));
-    size_t oKK1 = L.take(B * maxm * sizeof(int));
+    size_t oKK1 = L.take(B * maxm * sizeof(int)), oEx = L.take(B * maxm * sizeof(int));
     size_t oRho = L.take(B * maxm * 8);
     size_t oT1 = L.take((nm + 1) * sizeof(int)), oT2 = L.take((nm + 1) * sizeof(int));
     size_t oT3 = L.take((nm + 1) * sizeof(int));
@@ -416,16 +416,15 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
     setBand(p->bandr, (double*)nullptr);
     setBand(p->bandc, (cplx*)nullptr);
     DcWork& w = p->dc;
-    w.dw = (double*)(b + oDd[0]);
-    w.ds = (double*)(b + oDd[1]);
-    w.zs = (double*)(b + oDd[2]);
-    w.dfval = (double*)(b + oDd[3]);
-    w.dnd = (double*)(b + oDd[4]);
-    w.znd = (double*)(b + oDd[5]);
-    w.tau = (double*)(b + oDd[6]);
-    w.zhat = (double*)(b + oDd[7]);
-    w.cinv = (double*)(b + oDd[8]);
-    w.fval = (double*)(b + oDd[9]);
+    w.ds = (double*)(b + oDd[0]);
+    w.zs = (double*)(b + oDd[1]);
+    w.dfval = (double*)(b + oDd[2]);
+    w.dnd = (double*)(b + oDd[3]);
+    w.znd = (double*)(b + oDd[4]);
+    w.tau = (double*)(b + oDd[5]);
+    w.zhat = (double*)(b + oDd[6]);
+    w.cinv = (double*)(b + oDd[7]);
+    w.fval = (double*)(b + oDd[8]);
     w.rot_cs = (double*)(b + oRcs);
     w.perm = (int*)(b + oDi[0]);
     w.ndl = (int*)(b + oDi[1]);
@@ -436,6 +435,7 @@ size_t layout(const ks_plan_desc* d, ks_plan* p) {
     w.rot_idx = (int*)(b + oRidx);
     w.kk = (int*)(b + oKK);
     w.kk1 = (int*)(b + oKK1);
+    w.ex = (int*)(b + oEx);
     w.nrot = (int*)(b + oNR);
     w.rho = (double*)(b + oRho);
     DcTree& t = p->tree;

@@ -183,7 +183,6 @@ struct BandWork {
 // Divide-and-conquer scratch; all position-indexed arrays have n entries and
 // each merge uses the slice [lo, hi) of its rows.
 struct DcWork {
-    double* dw;
     double* ds;
     double* zs;
     int* perm;
@@ -204,6 +203,7 @@ struct DcWork {
     int* kk1;       // per merge: kept columns of the first child (< 0: columns not grouped)
     int* gpos;      // kept entry (secular order) -> its column in the child-grouped order
     int* nrot;
+    int* ex;        // per merge: its entries are scaled by 2^-ex
     double* rho;
 };
 

@@ -63,6 +63,12 @@ __device__ __forceinline__ T lane_sum(T v) {
     return sum21(sum4(sum8(v)));
 }
 
+// The value of lane l (uniform) in every lane.
+__device__ __forceinline__ double lane_get(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ cplx lane_get(cplx v, int l) { return mk(lane_get(v.x, l), lane_get(v.y, l)); }
+
 // The sums of R values over the wavefront at once: lane l ends with the sum of
 // value l / (64 / R).
 template <typename T>

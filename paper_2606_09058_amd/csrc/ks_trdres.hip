@@ -94,11 +94,6 @@ __device__ __forceinline__ double mk_<double>(double re, double) { return re; }
 template <>
 __device__ __forceinline__ cplx mk_<cplx>(double re, double im) { return mk(re, im); }
 
-__device__ __forceinline__ double lane_get(double v, int l) {  // l uniform
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-__device__ __forceinline__ cplx lane_get(cplx v, int l) { return mk(lane_get(v.x, l), lane_get(v.y, l)); }
-
 // H_k = I - tau v v^H from alpha = x_{k+1} and |x_{k+2..}|^2 (as in ks_hetrd.hip).
 template <typename T>
 __device__ __forceinline__ void form_reflector(T alpha, double xn2, T& sc, T& tv, double& beta) {
