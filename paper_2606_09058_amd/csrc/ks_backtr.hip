@@ -27,44 +27,73 @@ __global__ void load_z_kernel(int n, int ncols, const double* Z, int c0, T* X, i
 // The triangular factors of the BACKTR_SUB-reflector sub-blocks ("quarters"
 // of a 256-reflector block) of every block at once (blockIdx.x = block x
 // sub-blocks per block + sub-block, blockIdx.y = matrix): T_q solves
-// (diag(1/tau) + striu(G_qq)) T_q = I for the quarter's reflectors, by back
-// substitution on the identity, column c by thread c.  G_b (= V_b^H V_b) and
-// T_b share storage (leading dimension BT): each quarter reads its diagonal
-// block of G into LDS before writing T_q over it, and zeroes the blocks to its
+// (diag(1/tau) + striu(G_qq)) T_q = I for the quarter's reflectors.  Blocks of
+// 16 reflectors by back substitution on the identity (column c by lane c, the
+// unknowns in registers, each new one taken off the rows above at once), then
+// neighbours joined by T_12 = -T_1 G_12 T_2, 16 to 32 to 64, in LDS.  (One lane per
+// column of the whole quarter was a chain of 2016 multiply-adds: 50 us real, 130
+// complex at orders 64 and 520, now 18 and 26.)  G_b (= V_b^H V_b) and T_b share storage (leading dimension BT): each quarter reads its
+// diagonal block of G into LDS before writing T_q over it, and zeroes the blocks to its
 // left (T_b is upper triangular); the blocks above the diagonal still hold
 // V_p^H V_q for the coupling terms.
 constexpr int TF_Q = BACKTR_SUB;
+constexpr int TF_S = 16;  // reflectors per back substitution
 template <typename T>
-__global__ __launch_bounds__(TF_Q) void t_factors_kernel(int n, int B, const T* tau, T* Tall, long sT) {
-    constexpr int H = TF_Q;
+__global__ __launch_bounds__(256) void t_factors_kernel(int n, int B, const T* tau, T* Tall, long sT) {
+    constexpr int H = TF_Q, S = TF_S, NT = 256;
     const int nq = B / H;
-    const int b = blockIdx.x / nq, qd = blockIdx.x % nq, z = blockIdx.y;
+    const int b = blockIdx.x / nq, qd = blockIdx.x % nq, z = blockIdx.y, t = threadIdx.x;
     const int b0 = b * B, jb = min(B, n - 1 - b0), o = qd * H, jh = min(H, jb - o);
     if (jh <= 0) return;
     T* Tb = Tall + z * sT + (long)b * B * B;
     T* Th = Tb + (long)o * B + o;
     tau += (long)z * n + b0 + o;
-    __shared__ T sg[H][H + 1];
+    __shared__ T sg[H][H + 1];  // G above the diagonal, T on and above it as it is formed
+    __shared__ T sy[H / 2][H / 2 + 1];
     __shared__ T st[H];
-    for (int e = threadIdx.x; e < jh * jh; e += blockDim.x) sg[e / jh][e % jh] = Th[(long)(e / jh) * B + e % jh];
-    if ((int)threadIdx.x < jh) st[threadIdx.x] = tau[threadIdx.x];
-    __syncthreads();  // the quarter's block of G is in LDS before T_q overwrites it
-    const int c = threadIdx.x;
-    for (int i = 0; i < jh; ++i)
-        for (int cc = c; cc < o; cc += H) Tb[(long)(o + i) * B + cc] = zero_<T>();  // left of the quarter
-    if (c >= jh) return;
-    T w[H];
-#pragma unroll
-    for (int i = H - 1; i >= 0; --i) {
-        if (i < jh) {
-            T acc = (i == c) ? from_re<T>(1.0) : zero_<T>();
-#pragma unroll
-            for (int l = i + 1; l < H; ++l)
-                if (l < jh) acc -= sg[i][l] * w[l];
-            w[i] = st[i] * acc;
-            Th[(long)i * B + c] = w[i];
-        }
+    // (entries beyond a ragged quarter: zero G and tau, so T's there are zero)
+    for (int e = t; e < H * H; e += NT) {
+        const int i = e / H, j = e % H;
+        sg[i][j] = i < j && j < jh ? Th[(long)i * B + j] : zero_<T>();
     }
+    if (t < H) st[t] = t < jh ? tau[t] : zero_<T>();
+    for (int e = t; e < jh * o; e += NT) Tb[(long)(o + e / o) * B + e % o] = zero_<T>();  // left of the quarter
+    __syncthreads();
+    if (t < H) {
+        const int s0 = t / S * S, c = t % S;
+        T w[S];
+#pragma unroll
+        for (int i = 0; i < S; ++i) w[i] = i == c ? from_re<T>(1.0) : zero_<T>();
+#pragma unroll
+        for (int i = S - 1; i >= 0; --i) {
+            w[i] = st[s0 + i] * w[i];
+#pragma unroll
+            for (int l = 0; l < i; ++l) w[l] -= sg[s0 + l][s0 + i] * w[i];
+        }
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+            if (i <= c) sg[s0 + i][s0 + c] = w[i];
+    }
+    __syncthreads();
+    for (int hb = S; hb < H; hb *= 2) {
+        const int np = H / (2 * hb), tot = np * hb * hb;  // pairs, entries of their couplings
+        // Y = G_12 T_2 (upper triangular T_2: inner entries up to the column), then -T_1 Y
+        for (int e = t; e < tot; e += NT) {
+            const int pr = e / (hb * hb), i = e / hb % hb, j = e % hb, r0 = pr * 2 * hb, c0 = r0 + hb;
+            T y = zero_<T>();
+            for (int l = 0; l <= j; ++l) y += sg[r0 + i][c0 + l] * sg[c0 + l][c0 + j];
+            sy[pr * hb + i][j] = y;
+        }
+        __syncthreads();
+        for (int e = t; e < tot; e += NT) {
+            const int pr = e / (hb * hb), i = e / hb % hb, j = e % hb, r0 = pr * 2 * hb, c0 = r0 + hb;
+            T y = zero_<T>();
+            for (int l = i; l < hb; ++l) y -= sg[r0 + i][r0 + l] * sy[pr * hb + l][j];
+            sg[r0 + i][c0 + j] = y;
+        }
+        __syncthreads();
+    }
+    for (int e = t; e < jh * jh; e += NT) Th[(long)(e / jh) * B + e % jh] = sg[e / jh][e % jh];
 }
 
 // The compact-WY factors T_b (jb x jb, row-major with leading dimension BT, at
@@ -82,41 +111,44 @@ void backtransform_prepare(hipStream_t s, int n, int batch, const T* Vall, const
     if (nref <= 0) return;
     const int nblk = cdiv(nref, bt), nfull = nref / bt;
     const long sV = (long)n * n, bb = (long)bt * bt;
-    for (int z = 0; z < batch; ++z) {
-        const T* V = Vall + z * sV;
-        // G_b is staged where T_b goes
-        T* Gz = w.Tall + z * w.sTall;
-        if (nfull > 0)
-            gemm_splitk<T>(s, OP_C, OP_N, bt, bt, n, 1.0, V, n, V, n, 0.0, Gz, bt, w.P, w.pelems, nfull, bt, bt, bb);
-        if (nblk > nfull) {
-            const int b0 = nfull * bt, jb = nref - b0;
-            gemm_splitk<T>(s, OP_C, OP_N, jb, jb, n, 1.0, V + b0, n, V + b0, n, 0.0, Gz + (long)nfull * bb, bt,
-                           w.P, w.pelems);
-        }
+    const int jl = nref - nfull * bt;  // order of a ragged last block (0 if none)
+    // the launches take the full blocks of one matrix or one block of every
+    // matrix, whichever are more
+    const bool by_matrix = batch > nfull;
+    const int nout = by_matrix ? nfull : batch, nin = by_matrix ? batch : nfull;
+    const long so = by_matrix ? bb : w.sTall, si = by_matrix ? w.sTall : bb;
+    // G_b is staged where T_b goes
+    for (int q = 0; q < nout && nfull > 0; ++q) {
+        const T* V = Vall + (by_matrix ? q * (long)bt : q * sV);
+        const long sv = by_matrix ? sV : bt;
+        gemm_splitk<T>(s, OP_C, OP_N, bt, bt, n, 1.0, V, n, V, n, 0.0, w.Tall + q * so, bt, w.P, w.pelems, nin, sv, sv,
+                       si);
     }
-    hipLaunchKernelGGL((t_factors_kernel<T>), dim3((bt / TF_Q) * nblk, batch), dim3(TF_Q), 0, s, n, bt, tau, w.Tall,
+    if (jl > 0) {
+        const T* V = Vall + (long)nfull * bt;
+        gemm_splitk<T>(s, OP_C, OP_N, jl, jl, n, 1.0, V, n, V, n, 0.0, w.Tall + nfull * bb, bt, w.P, w.pelems, batch, sV,
+                       sV, w.sTall);
+    }
+    hipLaunchKernelGGL((t_factors_kernel<T>), dim3((bt / TF_Q) * nblk, batch), dim3(256), 0, s, n, bt, tau, w.Tall,
                        w.sTall);
     // join pairs: Y = G_12 T_2 (in W1), then T_12 = -T_1 Y over G_12
-    const int jl = nref - nfull * bt;  // order of a ragged last block (0 if none)
-    for (int z = 0; z < batch; ++z) {
-        T* Tz = w.Tall + z * w.sTall;
-        for (int hb = TF_Q; hb < bt; hb *= 2) {
-            for (int po = 0; po < bt; po += 2 * hb) {
-                T* T1 = Tz + (long)po * bt + po;
-                T* G12 = T1 + hb;
-                T* T2 = T1 + (long)hb * bt + hb;
-                if (nfull > 0) {
-                    gemm<T>(s, OP_N, OP_N, hb, hb, hb, 1.0, G12, bt, bb, T2, bt, bb, 0.0, w.W1, hb, (long)hb * hb,
-                            nfull);
-                    gemm<T>(s, OP_N, OP_N, hb, hb, hb, -1.0, T1, bt, bb, w.W1, hb, (long)hb * hb, 0.0, G12, bt, bb,
-                            nfull);
-                }
-                const int h2 = std::min(hb, jl - po - hb);  // the ragged block's second factor of this pair
-                if (nblk > nfull && h2 > 0) {
-                    const long lo = (long)nfull * bb;
-                    gemm<T>(s, OP_N, OP_N, hb, h2, h2, 1.0, G12 + lo, bt, 0, T2 + lo, bt, 0, 0.0, w.W1, h2, 0, 1);
-                    gemm<T>(s, OP_N, OP_N, hb, h2, hb, -1.0, T1 + lo, bt, 0, w.W1, h2, 0, 0.0, G12 + lo, bt, 0, 1);
-                }
+    for (int hb = TF_Q; hb < bt; hb *= 2) {
+        for (int po = 0; po < bt; po += 2 * hb) {
+            const long o1 = (long)po * bt + po, o12 = o1 + hb, o2 = o1 + (long)hb * bt + hb;
+            for (int q = 0; q < nout && nfull > 0; ++q) {
+                T* Tq = w.Tall + q * so;
+                gemm<T>(s, OP_N, OP_N, hb, hb, hb, 1.0, Tq + o12, bt, si, Tq + o2, bt, si, 0.0, w.W1, hb,
+                        (long)hb * hb, nin);
+                gemm<T>(s, OP_N, OP_N, hb, hb, hb, -1.0, Tq + o1, bt, si, w.W1, hb, (long)hb * hb, 0.0, Tq + o12, bt,
+                        si, nin);
+            }
+            const int h2 = std::min(hb, jl - po - hb);  // the ragged block's second factor of this pair
+            if (h2 > 0) {
+                T* Tq = w.Tall + nfull * bb;
+                gemm<T>(s, OP_N, OP_N, hb, h2, h2, 1.0, Tq + o12, bt, w.sTall, Tq + o2, bt, w.sTall, 0.0, w.W1, h2,
+                        (long)hb * h2, batch);
+                gemm<T>(s, OP_N, OP_N, hb, h2, hb, -1.0, Tq + o1, bt, w.sTall, w.W1, h2, (long)hb * h2, 0.0, Tq + o12,
+                        bt, w.sTall, batch);
             }
         }
     }
