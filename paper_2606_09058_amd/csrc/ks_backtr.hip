@@ -10,6 +10,7 @@
 // order shares every launch (GEMM batch index, or blockIdx.y / z selecting the
 // matrix).
 #include "ks_internal.hpp"
+#include "ks_lanes.hpp"
 
 namespace ks {
 
@@ -188,57 +189,131 @@ void load_z(hipStream_t s, int n, int batch, int ncols, const double* Z, int c0,
 }
 
 // ---------------------------------------------------------------- Fermi level
+// 1 / (1 + e^x); 0 or 1 to 4e-18 beyond 40, without an exponential.
 __device__ inline double fermi_F(double x) {
-    if (x > 0.0) {
-        double e = exp(-x);
-        return e / (1.0 + e);
-    }
-    return 1.0 / (1.0 + exp(x));
+    const double y = fabs(x);
+    if (y > 40.0) return x > 0.0 ? (y > 800.0 ? 0.0 : exp(-y)) : 1.0;
+    const double e = exp(-y), r = 1.0 / (1.0 + e);
+    return x > 0.0 ? e * r : r;
+}
+// The same for the electron count alone, where 4e-18 of a state is nothing.
+__device__ inline double fermi_count(double x) {
+    if (x > 40.0) return 0.0;
+    if (x < -40.0) return 1.0;
+    const double e = exp(-fabs(x)), r = 1.0 / (1.0 + e);
+    return x > 0.0 ? e * r : r;
 }
 
 // One workgroup: mu by bisection on sum_k w_k sum_i g F((eps_ik - mu)/kT) = ne over
 // [min eps - 50 kT, max eps + 50 kT] until hi - lo <= 1e-14 max(1, |mu|) (at most
 // 200 halvings), mu = midpoint; then occ, E_band and the window check.
+// A halving is a chain of exponentials, a sum over the workgroup and a barrier,
+// 1.5 us however few the eigenvalues.  The eigenvalues are therefore taken in
+// chunks of 64, of which only those within 40 kT of the point are looked at
+// (the others are full or empty, by their smallest and largest value): a lane
+// keeps what a wavefront has to know of one of its chunks.  Up to 64 chunks
+// every wavefront has them all, and the sixteen count at the 15 inner points
+// of four halvings at once; beyond, the wavefronts share the chunks of one count.
+// (Against all eigenvalues at every halving: order 64 76 -> 21 us, 8 x 208
+// 230 -> 108, 1300 106 -> 70, 16 x 1300 800 -> 158.)
+constexpr int FERMI_CHUNKS = 64;
 __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const double* eps,
                                                      KWeights kw, double g, double ne, double kT,
                                                      int il, int iu, double* occ, double* mu_out,
                                                      double* eband_out, int* kwin, int* info) {
-    __shared__ double red[16];
+    __shared__ double red[2][16];
+    __shared__ double se[FERMI_CHUNKS * 64];
     __shared__ int lastw[16];
-    int t = threadIdx.x;
-    long tot = (long)batch * order;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int per = (order + 63) / 64;  // chunks of a k-point
+    const long nchunk = (long)batch * per;
+    const bool few = nchunk <= FERMI_CHUNKS, held = nchunk <= 16 * 64;
+    // chunk c of the wavefront: c itself, or c * 16 + wave
+    auto chunk_id = [&](long c) { return few ? c : c * 16 + wave; };
     double mn = INFINITY, mx = -INFINITY;
-    for (long i = t; i < tot; i += blockDim.x) {
-        mn = fmin(mn, eps[i]);
-        mx = fmax(mx, eps[i]);
+    double cmin = INFINITY, cmax = INFINITY, cw = 0.0;  // of chunk `lane`: an absent one is empty
+    long cbase = 0;
+    int cnum = 0;
+    for (long c = 0; chunk_id(c) < nchunk; ++c) {
+        const long id = chunk_id(c), bq = id / per, base = bq * order + (id % per) * 64;
+        const int num = min(64, (int)((bq + 1) * order - base));
+        const bool in = lane < num;
+        const double e = in ? eps[base + lane] : 0.0;
+        if (few && wave == (int)(c & 15)) se[id * 64 + lane] = in ? e : INFINITY;
+        const double a = wave_min(in ? e : INFINITY), z = wave_max(in ? e : -INFINITY);
+        const bool nan = __any(e != e);  // such a chunk is neither full nor empty
+        mn = fmin(mn, a);
+        mx = fmax(mx, z);
+        if (lane == c) {
+            cmin = nan ? -INFINITY : a;
+            cmax = nan ? INFINITY : z;
+            cw = g * kw.w[bq];
+            cbase = few ? id * 64 : base;
+            cnum = num;
+        }
     }
-    mn = wave_min(mn);
-    mx = wave_max(mx);
-    __shared__ double smn[16], smx[16];
-    if ((t & 63) == 0) {
-        smn[t >> 6] = mn;
-        smx[t >> 6] = mx;
+    if (lane == 0) {
+        red[0][wave] = mn;
+        red[1][wave] = mx;
     }
     __syncthreads();
     double lo = INFINITY, hi = -INFINITY;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
-        lo = fmin(lo, smn[i]);
-        hi = fmax(hi, smx[i]);
+    for (int i = 0; i < 16; ++i) {
+        lo = fmin(lo, red[0][i]);
+        hi = fmax(hi, red[1][i]);
     }
     lo -= 50.0 * kT;
     hi += 50.0 * kT;
-    for (int it = 0; it < 200; ++it) {
-        double mid = 0.5 * (lo + hi);
-        if (hi - lo <= 1e-14 * fmax(1.0, fabs(mid))) break;
+    __syncthreads();
+    const double ikT = 1.0 / kT;
+    const double* src = few ? se : eps;
+    // the wavefront's chunks' electrons at x, in every lane
+    auto count = [&](double x) {
         double cnt = 0.0;
-        for (int b = 0; b < batch; ++b) {
-            double sb = 0.0;
-            for (int i = t; i < order; i += blockDim.x) sb += fermi_F((eps[(long)b * order + i] - mid) / kT);
-            cnt += kw.w[b] * g * sb;
+        if (held) {
+            bool act = false;
+            if ((cmax - x) * ikT < -40.0) cnt = cw * cnum;
+            else act = !((cmin - x) * ikT > 40.0);
+            unsigned long long mask = __ballot(act && cnum > 0);
+            while (mask) {
+                const int l = __builtin_amdgcn_readfirstlane(__ffsll(mask) - 1);
+                mask &= mask - 1;
+                const long base = __builtin_amdgcn_readlane((int)cbase, l);
+                const int num = __builtin_amdgcn_readlane(cnum, l);
+                if (lane < num) cnt += lane_get(cw, l) * fermi_count((src[base + lane] - x) * ikT);
+            }
+        } else {
+            for (int b = 0; b < batch; ++b) {
+                double sb = 0.0;
+                for (int i = t; i < order; i += 1024) sb += fermi_count((eps[(long)b * order + i] - x) * ikT);
+                cnt += g * kw.w[b] * sb;
+            }
         }
-        cnt = block_sum(cnt, red);
-        if (cnt < ne) lo = mid;
-        else hi = mid;
+        return lane_sum(cnt);
+    };
+    for (int it = 0; it < (few ? 50 : 200); ++it) {
+        const double mid = 0.5 * (lo + hi);
+        if (hi - lo <= 1e-14 * fmax(1.0, fabs(mid))) break;
+        double* rd = red[it & 1];
+        // wavefront w of few chunks counts at lo + (w + 1) / 16 (hi - lo)
+        const double cnt = count(few ? lo + 0.0625 * (wave + 1) * (hi - lo) : mid);
+        if (lane == 0) rd[wave] = cnt;
+        __syncthreads();
+        if (few) {
+            int p = 0;  // the path of four halvings among the points
+#pragma unroll
+            for (int s = 8; s > 0; s >>= 1)
+                if (rd[p + s - 1] < ne) p += s;
+            const double w = hi - lo, l0 = lo;
+            lo = l0 + 0.0625 * p * w;
+            hi = p < 15 ? l0 + 0.0625 * (p + 1) * w : hi;
+        } else {
+            double sum = 0.0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum += rd[i];
+            if (sum < ne) lo = mid;
+            else hi = mid;
+        }
     }
     double mu = 0.5 * (lo + hi);
     double eb = 0.0;
@@ -256,7 +331,8 @@ __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const
         }
         eb += kw.w[b] * sb;
     }
-    eb = block_sum(eb, red);
+    __syncthreads();
+    eb = block_sum(eb, red[0]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
     if ((t & 63) == 0) lastw[t >> 6] = last;
