@@ -790,7 +790,25 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
     int k0 = 0;
     for (; n - k0 > mres; k0 += nb) {
         int jb = min(nb, n - 1 - k0);
-        for (int q = 0; q < ng; ++q) {
+        // one launch per panel for a single matrix on the whole chip: 8.8 to 21 us per
+        // column where the two launches take 20 to 32 (real, trailing orders 3100 to 6656),
+        // 11 to 120 where they take 16 to 130 (complex, 2080 to 9984)
+        const bool panel = batch == 1 && w.gang.mem && w.gang.ncu >= 256 && jb == nb && n - k0 <= panel_order<T>() &&
+                           (long)(n - k0) * lda * (long)sizeof(S) < 1L << 32;
+        if (panel) {
+            const bool smp = w.prof && w.prof->sample();
+            hipEvent_t e0 = smp ? w.prof->take() : nullptr;
+            hipEvent_t e1 = smp ? w.prof->take() : nullptr;
+            if (smp) (void)hipEventRecord(e0, s);
+            hetrd_panel<T, S>(s, n, k0, A, lda, d, e, tau, Vall, w.VW, w.WV, w.gang, w.info);
+            if (smp) {
+                (void)hipEventRecord(e1, s);
+                double bytes = 0.0;
+                for (int m = n - k0 - 1; m > n - k0 - 1 - nb; --m) bytes += (double)sizeof(S) * m * (m + 1) / 2.0;
+                w.prof->push(PROF_HEMV, e0, e1, bytes);
+            }
+        }
+        for (int q = 0; q < ng && !panel; ++q) {
             TrdGroup<T, S>& G = g[q];
             // The column kernels write every panel row the trailing update and
             // the next columns read (rows k+1.. of column k); only a short last
@@ -802,7 +820,7 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
             hipLaunchKernelGGL((colstart_kernel<T, S>), dim3(partial_blocks<S>(n, k0), 1, G.B), dim3(64), 0, G.s, n,
                                k0, nb, G.A, lda, sA, G.w);
         }
-        for (int j = 0; j < jb; ++j) {
+        for (int j = 0; j < jb && !panel; ++j) {
             int k = k0 + j;
             int m = n - k - 1;
             const int sch = w.sch_for(k);

@@ -284,6 +284,23 @@ void hetrd_resident(hipStream_t s, int n, int k0, S* A, int lda, long sA, int ba
 // Entries per matrix that GangWork::mem needs for a plan of this order.
 template <typename T>
 long gang_mem(int order, int batch);
+// A panel of HETRD_NB columns of one matrix of trailing order n - k0 in one launch
+// (ks_trdpanel.hip), with the trailing matrix and the panel buffers as after the
+// two launches per column; up to which trailing order.
+template <typename T, typename S>
+void hetrd_panel(hipStream_t s, int n, int k0, S* A, int lda, double* d, double* e, T* tau, T* Vall, T* VW, T* WV,
+                 GangWork<T> gw, int* info);
+template <typename T>
+int panel_order();
+// For it: how long its forms wait for their workgroups (1: the chip, 2: a quarter),
+// the gang's state and `words` exchange entries at p made ready, and one
+// workgroup behind it that does the columns if neither form gathered.
+long long gang_gate(int form);
+template <typename T>
+void gang_open(hipStream_t s, GangWork<T> gw, T* p, long words);
+template <typename T, typename S>
+void trd_single_panel(hipStream_t s, int n, int k0, int kend, S* A, int lda, T* Vall, double* d, double* e, T* tau,
+                      T* VW, T* WV, GangWork<T> gw);
 // Test hook, for the launches of the calling thread: 1 = the gangs that take the
 // whole chip leave at once, 2 = every gang does, 0 = none.
 void trd_set_leave(int level);

@@ -45,76 +45,12 @@
 // takes the whole chip, one workgroup (trd_single_kernel) behind the others.
 // Waits inside a gang that is complete are bounded as well
 // (KS_ERR_NO_CONVERGENCE, detail -4).
-#include "ks_internal.hpp"
+#include "ks_gang.hpp"
 #include "ks_lanes.hpp"
 
 namespace ks {
 
 namespace {
-
-typedef unsigned long long u64;
-constexpr u64 EMPTY = 0x7ff4a5a5deadbeefULL;  // a signalling NaN: no operation returns it
-constexpr long long TICKS = 100000;           // wall_clock64() ticks per millisecond
-constexpr long long GATE_MS = 1000, CHIP_GATE_MS = 3, WAIT_MS = 4000;
-enum { GANG_NONE = 0, GANG_GO = 1, GANG_LEFT = 2, GANG_FAILED = 3 };
-
-__device__ __forceinline__ void publish(double* p, double v) {
-    u64 b = (u64)__double_as_longlong(v);
-    if (b == EMPTY) b ^= 1;
-    __hip_atomic_store((u64*)p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void publish(cplx* p, cplx v) {
-    publish(&p->x, v.x);
-    publish(&p->y, v.y);
-}
-__device__ __forceinline__ void empty_out(double* p) {
-    __hip_atomic_store((u64*)p, EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void empty_out(cplx* p) {
-    empty_out(&p->x);
-    empty_out(&p->y);
-}
-__device__ __forceinline__ double peek(const double* p) {
-    return __longlong_as_double((long long)__hip_atomic_load((const u64*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-__device__ __forceinline__ cplx peek(const cplx* p) { return mk(peek(&p->x), peek(&p->y)); }
-__device__ __forceinline__ bool is_empty(double v) { return (u64)__double_as_longlong(v) == EMPTY; }
-template <typename T>
-__device__ __forceinline__ T empty_();
-template <>
-__device__ __forceinline__ double empty_<double>() { return __longlong_as_double((long long)EMPTY); }
-template <>
-__device__ __forceinline__ cplx empty_<cplx>() { return mk(empty_<double>(), empty_<double>()); }
-__device__ __forceinline__ bool is_empty(cplx v) { return is_empty(v.x) || is_empty(v.y); }
-
-template <typename T>
-__device__ __forceinline__ T mk_(double re, double im);
-template <>
-__device__ __forceinline__ double mk_<double>(double re, double) { return re; }
-template <>
-__device__ __forceinline__ cplx mk_<cplx>(double re, double im) { return mk(re, im); }
-
-// H_k = I - tau v v^H from alpha = x_{k+1} and |x_{k+2..}|^2 (as in ks_hetrd.hip).
-template <typename T>
-__device__ __forceinline__ void form_reflector(T alpha, double xn2, T& sc, T& tv, double& beta) {
-    const double ar = re_(alpha), ai = im_(alpha);
-    if (xn2 == 0.0 && ai == 0.0) {
-        tv = zero_<T>();
-        beta = ar;
-        sc = zero_<T>();
-    } else {
-        beta = -copysign(sqrt(ar * ar + ai * ai + xn2), ar);
-        tv = mk_<T>((beta - ar) / beta, -ai / beta);
-        sc = inv_(alpha - from_re<T>(beta));
-    }
-}
-
-// acc += a b, a fused multiply-add per real product
-__device__ __forceinline__ void fma_(double& acc, double a, double b) { acc = fma(a, b, acc); }
-__device__ __forceinline__ void fma_(cplx& acc, cplx a, cplx b) {
-    acc.x = fma(-a.y, b.y, fma(a.x, b.x, acc.x));
-    acc.y = fma(a.y, b.x, fma(a.x, b.y, acc.y));
-}
 
 // Entry (i, j) of the trailing matrix from its lower triangle.
 template <typename T, typename S>
@@ -547,12 +483,13 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
 // work leaves at once.
 __device__ int g_chip = 0;
 
-// Before a gang: its buffers empty, its state cleared, the chip taken if it
-// needs that.
+// Before a gang: its buffers empty (those of a panel: words entries at p), its
+// state cleared, the chip taken if it needs that.
 template <typename T>
-__global__ void gang_init_kernel(GangWork<T> gw, int slotn, int chip) {
+__global__ void gang_init_kernel(GangWork<T> gw, int slotn, int chip, T* p, long words) {
     const int z = blockIdx.y;
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    for (long e = i; e < words; e += (long)gridDim.x * blockDim.x) empty_out(&p[e]);
     if (i < 3 * slotn) {
         empty_out(&gw.xp[z * gw.sxp + i]);
         empty_out(&gw.xr[z * gw.sxr + i]);
@@ -571,10 +508,13 @@ __global__ void gang_init_kernel(GangWork<T> gw, int slotn, int chip) {
 // Behind a gang (and, with mem, behind its form in memory): gives the chip
 // back, and where the gang could not gather its workgroups does columns 0 ..
 // kend-1 of the trailing matrix with one workgroup, in place in global memory.
-// The vectors v, w live in the gang's exchange buffer.
+// The vectors v, w live at vb, the gang's exchange buffer.  For a panel (VW not
+// null; kend = HETRD_NB) the reflectors go to the panel's buffer too, and WV becomes
+// zero: the trailing update has been done.
 template <typename T, typename S>
 __global__ __launch_bounds__(1024) void trd_single_kernel(int n, int k0, int kend, S* A, int lda, long sA, T* Vall,
-                                                          double* d, double* e, T* taua, GangWork<T> gw, int mem) {
+                                                          double* d, double* e, T* taua, GangWork<T> gw, int mem,
+                                                          T* vb, long svb, T* VW, T* WV) {
     __shared__ double red[16];
     const int t = threadIdx.x, NT = blockDim.x, z = blockIdx.x, m = n - k0;
     const int* state = gw.state + GANG_STATE * z;
@@ -585,7 +525,7 @@ __global__ __launch_bounds__(1024) void trd_single_kernel(int n, int k0, int ken
     d += (long)z * n + k0;
     e += (long)z * n + k0;
     taua += (long)z * n + k0;
-    T* v = gw.xr + z * gw.sxr;
+    T* v = vb + z * svb;
     T* w = v + m;
     zero_above<T>(n, k0, kend, Vall, 0, 1, t, NT);
     T* V = Vall + (long)k0 * n + k0;
@@ -626,6 +566,14 @@ __global__ __launch_bounds__(1024) void trd_single_kernel(int n, int k0, int ken
         __syncthreads();
     }
     if (t == 0 && kend >= m - 1) d[m - 1] = re_(widen(A[(long)(m - 1) * lda + m - 1]));
+    if (!VW) return;
+    for (int c = 0; c < HETRD_NB; ++c)
+        for (int i = c + 1 + t; i < m; i += NT) {
+            VW[(long)c * n + k0 + i] = V[(long)i * n + c];
+            VW[(long)(HETRD_NB + c) * n + k0 + i] = zero_<T>();
+            WV[(long)c * n + k0 + i] = zero_<T>();
+            WV[(long)(HETRD_NB + c) * n + k0 + i] = zero_<T>();
+        }
 }
 
 // ---------------------------------------------------------------- host side
@@ -638,7 +586,8 @@ void gang_run(hipStream_t s, int n, int k0, int kend, int B, S* A, int lda, long
               T* tau, GangWork<T>& gw, int* info) {
     static_assert(NT * C == R << LP && NT * C <= GANG_ORDER, "columns");
     const long long gate = (g_leave > (CHIP ? 0 : 1)) ? 0 : (CHIP ? CHIP_GATE_MS : GATE_MS) * TICKS;
-    hipLaunchKernelGGL((gang_init_kernel<T>), dim3(cdiv(3 * NT * C, 256), B), dim3(256), 0, s, gw, NT * C, (int)CHIP);
+    hipLaunchKernelGGL((gang_init_kernel<T>), dim3(cdiv(3 * NT * C, 256), B), dim3(256), 0, s, gw, NT * C, (int)CHIP,
+                       (T*)nullptr, 0L);
     hipLaunchKernelGGL((trd_gang_kernel<T, S, NT, C, R, WPE, false>), dim3(1 << LP, B), dim3(NT), 0, s, n, k0, kend,
                        LP, A, lda, sA, Vall, d, e, tau, gw, gate, info);
     if constexpr (CHIP) {
@@ -648,7 +597,7 @@ void gang_run(hipStream_t s, int n, int k0, int kend, int B, S* A, int lda, long
                            kend, 7, A, lda, sA, Vall, d, e, tau, gw, g2, info);
     }
     hipLaunchKernelGGL((trd_single_kernel<T, S>), dim3(B), dim3(1024), 0, s, n, k0, kend, A, lda, sA, Vall, d, e, tau,
-                       gw, (int)CHIP);
+                       gw, (int)CHIP, gw.xr, gw.sxr, (T*)nullptr, (T*)nullptr);
 }
 
 // A shape of the gang: the largest order it takes, its workgroups per matrix
@@ -729,6 +678,20 @@ void gang_columns(int shape, hipStream_t s, int n, int k0, int kend, int B, S* A
 
 void trd_set_leave(int level) { g_leave = level; }
 
+long long gang_gate(int form) { return g_leave >= form ? 0 : (form == 1 ? CHIP_GATE_MS : GATE_MS) * TICKS; }
+
+template <typename T>
+void gang_open(hipStream_t s, GangWork<T> gw, T* p, long words) {
+    hipLaunchKernelGGL((gang_init_kernel<T>), dim3(1024), dim3(256), 0, s, gw, 0, 1, p, words);
+}
+
+template <typename T, typename S>
+void trd_single_panel(hipStream_t s, int n, int k0, int kend, S* A, int lda, T* Vall, double* d, double* e, T* tau,
+                      T* VW, T* WV, GangWork<T> gw) {
+    hipLaunchKernelGGL((trd_single_kernel<T, S>), dim3(1), dim3(1024), 0, s, n, k0, kend, A, lda, 0L, Vall, d, e, tau,
+                       gw, 1, gw.mem, 0L, VW, WV);
+}
+
 // Gangs up to the largest order where one is faster than the two launches of a
 // column (which overlap for the two halves of a batch: bound by the bytes of
 // the product there).
@@ -794,12 +757,16 @@ void hetrd_resident(hipStream_t s, int n, int k0, S* A, int lda, long sA, int B,
 
 #define KS_INST(T, S)                                                                                          \
     template void hetrd_resident<T, S>(hipStream_t, int, int, S*, int, long, int, double*, double*, T*, T*,     \
-                                       GangWork<T>, int*);
+                                       GangWork<T>, int*);                                                      \
+    template void trd_single_panel<T, S>(hipStream_t, int, int, int, S*, int, T*, double*, double*, T*, T*, T*,  \
+                                         GangWork<T>);
 KS_INST(double, double)
 KS_INST(cplx, cplx)
 KS_INST(double, float)
 KS_INST(cplx, cplx32)
 #undef KS_INST
+template void gang_open<double>(hipStream_t, GangWork<double>, double*, long);
+template void gang_open<cplx>(hipStream_t, GangWork<cplx>, cplx*, long);
 template int resident_order<double>(int, int);
 template int resident_order<cplx>(int, int);
 template long gang_mem<double>(int, int);
