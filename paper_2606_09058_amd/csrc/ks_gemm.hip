@@ -405,19 +405,30 @@ struct Big<cplx32> {
     static constexpr int BM = 128, BN = 128, BK = 16;
 };
 
+// Which element of a block with rows of C a thread takes as its i-th of E, counted
+// along the rows: FP64 element t + 256 i, so that neighbours load and, in the
+// layout of the LDS tiles, write neighbours (with a run of elements per thread
+// bank conflicts took 23 % of the time of a complex product: 71 -> 77 TFLOP/s at
+// order 4992); FP32 a run (its larger tiles have no registers for E addresses).
+template <typename T>
+constexpr bool BIG_RUN = sizeof(T) == 4 || std::is_same<T, cplx32>::value;
+template <typename T, int E>
+__device__ inline int big_elem(int t, int i) {
+    return BIG_RUN<T> ? t * E + i : t + 256 * i;
+}
 // Load an R x C block of memory (row stride ld, C contiguous) starting at
-// (r0, c0), zero outside rows < nr and columns < nc; every thread takes one
-// contiguous run of R C / 256 elements.
+// (r0, c0), zero outside rows < nr and columns < nc.
 template <typename T, int R, int C, int OP>
 __device__ inline void big_load(T (&v)[R * C / 256], const T* P, int ld, int nr, int nc, int r0, int c0,
                                 int t) {
-    constexpr int E = R * C / 256, TPR = C / E;
-    static_assert(E * 256 == R * C && TPR * E == C && 256 / TPR == R, "block shape");
-    const int rr = r0 + t / TPR, cc = c0 + (t % TPR) * E;
+    constexpr int E = R * C / 256;
+    static_assert(E * 256 == R * C && C % E == 0 && (256 % C == 0 || C % 256 == 0), "block shape");
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-        const bool ok = rr < nr && cc + i < nc;
-        v[i] = ok ? ld_op<T, OP>(P + (long)rr * ld + cc + i) : zero_<T>();
+        const int e = big_elem<T, E>(t, i);
+        const int rr = r0 + (BIG_RUN<T> ? t / (C / E) : e / C), cc = c0 + (BIG_RUN<T> ? t % (C / E) * E + i : e % C);
+        const bool ok = rr < nr && cc < nc;
+        v[i] = ok ? ld_op<T, OP>(P + (long)rr * ld + cc) : zero_<T>();
     }
 }
 
@@ -428,9 +439,22 @@ __global__ __launch_bounds__(256, 2) void gemm_big_kernel(int m, int n, int K, d
     constexpr int BM = Big<T>::BM, BN = Big<T>::BN, BKb = Big<T>::BK;
     constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 16, NI = WN / 16;
     constexpr int EA = BM * BKb / 256, EB = BN * BKb / 256;
-    __shared__ T sA[2][BKb][BM + LPAD];
-    __shared__ T sB[2][BKb][BN + LPAD];
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    constexpr int PAD = std::is_same<T, cplx>::value ? 1 : LPAD;  // 16 rows of a column in different banks
+    __shared__ T sA[2][BKb][BM + PAD];
+    __shared__ T sB[2][BKb][BN + PAD];
+    int bx = blockIdx.x, by = blockIdx.y;
+    if (uplo == UPLO_FULL && tri == TRI_NONE) {
+        // Consecutive workgroups go to the eight dies in turn: each die gets a run of
+        // tiles of its own, in bands of eight tile rows, so that its L2 serves the
+        // rows and columns its tiles share.
+        const int gx = gridDim.x, gy = gridDim.y, tot = gx * gy, per = tot / 8;
+        int l = by * gx + bx;
+        if (l < 8 * per) l = (l % 8) * per + l / 8;
+        const int band = l / (8 * gx), r = min(8, gy - 8 * band), w = l - band * 8 * gx;
+        by = 8 * band + w % r;
+        bx = w / r;
+    }
+    const int m0 = by * BM, n0 = bx * BN;
     if (!in_uplo(uplo, m0 + BM - 1, n0)) return;  // tile strictly above the diagonal
     const long b = blockIdx.z;
     A += b * sa;
@@ -452,27 +476,17 @@ __global__ __launch_bounds__(256, 2) void gemm_big_kernel(int m, int n, int K, d
         else big_load<T, BN, BKb, OPB>(rb, B, ldb, n, K, n0, k0, t);
     };
     auto store = [&](int buf) {
-        if constexpr (OPA == OP_N) {
-            constexpr int TPR = BKb / EA;
-            const int mm = t / TPR, kk = (t % TPR) * EA;
 #pragma unroll
-            for (int i = 0; i < EA; ++i) sA[buf][kk + i][mm] = ra[i];
-        } else {
-            constexpr int TPR = BM / EA;
-            const int kk = t / TPR, mm = (t % TPR) * EA;
-#pragma unroll
-            for (int i = 0; i < EA; ++i) sA[buf][kk][mm + i] = ra[i];
+        for (int i = 0; i < EA; ++i) {
+            const int e = big_elem<T, EA>(t, i);
+            if constexpr (OPA == OP_N) sA[buf][e % BKb][e / BKb] = ra[i];
+            else sA[buf][e / BM][e % BM] = ra[i];
         }
-        if constexpr (OPB == OP_N) {
-            constexpr int TPR = BN / EB;
-            const int kk = t / TPR, nn = (t % TPR) * EB;
 #pragma unroll
-            for (int i = 0; i < EB; ++i) sB[buf][kk][nn + i] = rb[i];
-        } else {
-            constexpr int TPR = BKb / EB;
-            const int nn = t / TPR, kk = (t % TPR) * EB;
-#pragma unroll
-            for (int i = 0; i < EB; ++i) sB[buf][kk + i][nn] = rb[i];
+        for (int i = 0; i < EB; ++i) {
+            const int e = big_elem<T, EB>(t, i);
+            if constexpr (OPB == OP_N) sB[buf][e / BN][e % BN] = rb[i];
+            else sB[buf][e % BKb][e / BKb] = rb[i];
         }
     };
     const int lane = t & 63, w = t >> 6, wm = w >> 1, wn = w & 1;
