@@ -10,6 +10,7 @@
 // spin block, i.e. (I2 (x) L)^-1 H (I2 (x) L)^-H, by treating the 2n x 2n
 // matrix as two n-row (then n-column) blocks: a batch of 2 with a block stride.
 #include "ks_internal.hpp"
+#include "ks_lanes.hpp"
 
 namespace ks {
 
@@ -95,6 +96,123 @@ __global__ __launch_bounds__(64 * LW) void potrf_inv_leaf_kernel(int nb, T* A, i
     }
 }
 
+// 1 / sqrt(d) to a unit or two in the last place: the hardware's estimate and one
+// step of third order.
+__device__ __forceinline__ double rsqrt_(double d) {
+    const double y = __builtin_amdgcn_rsq(d), e = fma(-d * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// The same for real data.  Wavefront w holds the columns of panel w (16 of
+// them), lane i its row i: a panel is factored within its wavefront by lane
+// broadcasts, without a barrier, and the later panels take it off from LDS; then
+// each wavefront inverts a diagonal 16 x 16 block, and the inverse blocks are
+// joined by X_21 = -X_22 (L_21 X_11), 16 to 32 to 64.  Bound by the chain of 64
+// pivots: 22 to 23 us against 36 to 41 for the kernel above.  (Complex columns, with four lane
+// broadcasts for each entry, took 55 this way against 43.)
+constexpr int LS = 16;  // columns of a panel
+__global__ __launch_bounds__(CB / LS * 64) void potrf_inv_panels_kernel(int nb, double* A, int lda, long sa, double* D,
+                                                                      int ldd, long sd, int col0, int* info) {
+    __shared__ double sL[CB][CB + 1];
+    __shared__ double sX[CB][CB + 1];
+    __shared__ double sY[CB / 2][CB / 2 + 1];
+    __shared__ double rl[CB];
+    constexpr int NT = CB / LS * 64;
+    A += blockIdx.x * sa;
+    D += blockIdx.x * sd;
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    double a[LS];
+#pragma unroll
+    for (int c = 0; c < LS; ++c) {  // (rows beyond the block: of the identity)
+        const int j = LS * w + c;
+        const double x = A[(long)min(lane, nb - 1) * lda + min(min(j, lane), nb - 1)];
+        a[c] = pick(lane < nb, pick(j <= lane, x, 0.0), (j == lane ? 1.0 : 0.0));
+    }
+    for (int p = 0; p < CB / LS; ++p) {
+        const int j0 = LS * p;
+        if (w == p) {
+            int first = 0;
+            double rlv = 1.0;
+#pragma unroll
+            for (int c = 0; c < LS; ++c) {
+                const double d = lane_get(a[c], j0 + c);
+                const bool bad = !(d > 0.0) || !isfinite(d);
+                first = bad && first == 0 ? j0 + c + 1 : first;
+                const double dj = bad ? 1.0 : d, y = rsqrt_(dj);
+                a[c] = pick(lane > j0 + c, a[c] * y, (lane == j0 + c ? dj * y : 0.0));
+                rlv = lane == c ? y : rlv;
+                sL[lane][j0 + c] = a[c];
+#pragma unroll
+                for (int c2 = c + 1; c2 < LS; ++c2) a[c2] -= a[c] * lane_get(a[c], j0 + c2);
+            }
+            if (lane < LS) rl[j0 + lane] = rlv;
+            if (first && lane == 0) set_info(info, KS_ERR_NOT_POSDEF, col0 + first);
+        }
+        __syncthreads();
+        if (w > p) {
+#pragma unroll 4
+            for (int k = 0; k < LS; ++k) {
+                const double l = sL[lane][j0 + k];
+#pragma unroll
+                for (int c = 0; c < LS; ++c) a[c] -= l * sL[LS * w + c][j0 + k];
+            }
+        }
+    }
+    if (lane < LS) {
+        const int j0 = LS * w;
+        double x[LS];
+#pragma unroll
+        for (int i = 0; i < LS; ++i) x[i] = (i == lane ? 1.0 : 0.0);
+#pragma unroll
+        for (int k = 0; k < LS; ++k) {
+            asm volatile("" ::: "memory");  // one column's LDS reads at a time
+            x[k] = x[k] * rl[j0 + k];
+#pragma unroll
+            for (int i = k + 1; i < LS; ++i) x[i] -= sL[j0 + i][j0 + k] * x[k];
+            sX[j0 + k][j0 + lane] = x[k];
+        }
+    }
+    __syncthreads();
+    auto join = [&](auto half) {
+        constexpr int hb = decltype(half)::value, np = CB / (2 * hb), RW = NT / (np * hb), RT = hb / RW;
+        // RT rows of one column per thread, RW apart
+        const int pr = t / (NT / np), u = t % (NT / np), j = u % hb, i0 = u / hb, r0 = pr * 2 * hb, r1 = r0 + hb;
+        double y[RT];
+#pragma unroll
+        for (int q = 0; q < RT; ++q) y[q] = 0.0;
+#pragma unroll
+        for (int l = 0; l < hb; ++l) {  // (X_11 is lower triangular)
+            const double x = l >= j ? sX[r0 + l][r0 + j] : 0.0;
+#pragma unroll
+            for (int q = 0; q < RT; ++q) y[q] += sL[r1 + i0 + RW * q][r0 + l] * x;
+        }
+#pragma unroll
+        for (int q = 0; q < RT; ++q) sY[pr * hb + i0 + RW * q][j] = y[q];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < RT; ++q) y[q] = 0.0;
+#pragma unroll
+        for (int l = 0; l < hb; ++l) {
+            const double x = sY[pr * hb + l][j];
+#pragma unroll
+            for (int q = 0; q < RT; ++q) {
+                const int i = i0 + RW * q;
+                y[q] -= (l <= i ? sX[r1 + i][r1 + l] : 0.0) * x;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < RT; ++q) sX[r1 + i0 + RW * q][r0 + j] = y[q];
+        __syncthreads();
+    };
+    if (nb > LS) join(std::integral_constant<int, LS>());
+    if (nb > 2 * LS) join(std::integral_constant<int, 2 * LS>());
+    for (int i = w; i < nb; i += NT / 64)
+        if (lane < nb) {
+            if (lane <= i) A[(long)i * lda + lane] = sL[i][lane];
+            D[(long)i * ldd + lane] = lane <= i ? sX[i][lane] : 0.0;
+        }
+}
+
 // dst (rows x cols, ld ldd) = src (ld lds) for a batch.
 template <typename T>
 __global__ void copy_block_kernel(int rows, int cols, const T* src, int lds, long ss, T* dst, int ldd, long sd) {
@@ -108,8 +226,12 @@ template <typename T>
 static void potrf_inv_rec(hipStream_t s, int n, T* L, int ldl, long sl, T* Li, int ldi, long si, T* Tw, long st,
                           int batch, int col0, int* info) {
     if (n <= CB) {
-        hipLaunchKernelGGL((potrf_inv_leaf_kernel<T>), dim3(batch), dim3(64 * LW), 0, s, n, L, ldl, sl, Li, ldi, si,
-                           col0, info);
+        if constexpr (is_cplx<T>::value)
+            hipLaunchKernelGGL((potrf_inv_leaf_kernel<T>), dim3(batch), dim3(64 * LW), 0, s, n, L, ldl, sl, Li, ldi, si,
+                               col0, info);
+        else
+            hipLaunchKernelGGL(potrf_inv_panels_kernel, dim3(batch), dim3(CB / LS * 64), 0, s, n, L, ldl, sl, Li, ldi,
+                               si, col0, info);
         return;
     }
     int n1 = ((n / 2 + CB - 1) / CB) * CB;
