@@ -7,7 +7,7 @@
 // exchange (0.75 us from the store to the last reader) and of two barriers.
 // Measured, whole tridiagonalisation: order 64 real 0.70 -> 0.07 ms, 333 real
 // 4.0 -> 0.68, 520 complex 9.1 -> 1.6, 1024 real 13.1 -> 2.4, 1300 complex
-// 24.4 -> 5.0, 2048 complex 40.5 -> 12.0, 2600 real 36.7 -> 10.0, 16 x 1300
+// 24.4 -> 5.0, 2048 complex 40.5 -> 11.0, 2600 real 36.7 -> 7.7, 16 x 1300
 // complex 41.7 -> 27.5 ms.
 //
 // A gang of workgroups owns the full rows of the trailing matrix cyclically
@@ -611,12 +611,15 @@ struct GangShape {
     double us;
 };
 constexpr int CHIP_CUS = 256;
-// us per column measured on an MI355X; the two-launch column costs 12 to 15
+// us per column measured on an MI355X (the largest shape of each type keeps some
+// of its registers in scratch memory; the one below it takes over as soon as it can:
+// 2600 real 13.8 -> 11.5 ms, 2048 complex with its backward pass 26.8 -> 26.1); the two-launch column costs 12 to 15
 // (real) and 16 to 23 (complex) at these orders
 constexpr GangShape SHAPES_R[] = {{256, 5, 8, 2.0}, {512, 6, 16, 2.1}, {1024, 7, 64, 2.45}, {2048, 8, CHIP_CUS, 2.85},
-                                  {3072, 8, CHIP_CUS, 5.7}};
+                                  {2560, 8, CHIP_CUS, 3.7}, {3072, 8, CHIP_CUS, 8.3}};
 constexpr GangShape SHAPES_C[] = {{256, 5, 8, 2.5},   {512, 6, 32, 2.9},          {512, 4, 16, 4.8},
-                                  {1024, 6, 64, 4.35}, {1536, 8, CHIP_CUS, 4.45}, {2048, 8, CHIP_CUS, 9.4}};
+                                  {1024, 6, 64, 4.35}, {1536, 8, CHIP_CUS, 4.45}, {1792, 8, CHIP_CUS, 8.5},
+                                  {2048, 8, CHIP_CUS, 12.0}};
 constexpr int NSHAPE_R = sizeof(SHAPES_R) / sizeof(GangShape), NSHAPE_C = sizeof(SHAPES_C) / sizeof(GangShape);
 template <typename T>
 const GangShape* shapes(int& n) {
@@ -661,7 +664,8 @@ void gang_columns(int shape, hipStream_t s, int n, int k0, int kend, int B, S* A
             case 2: return gang_run<T, S, 512, 1, 32, 4, 2, false>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
             case 3: return gang_run<T, S, 512, 2, 16, 6, 2, false>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
             case 4: return gang_run<T, S, 512, 3, 6, 8, 2, true>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
-            case 5: return gang_run<T, S, 512, 4, 8, 8, 2, true>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
+            case 5: return gang_run<T, S, 448, 4, 7, 8, 2, true>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
+            case 6: return gang_run<T, S, 512, 4, 8, 8, 2, true>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
         }
     } else {
         switch (shape) {
@@ -669,7 +673,8 @@ void gang_columns(int shape, hipStream_t s, int n, int k0, int kend, int B, S* A
             case 1: return gang_run<T, S, 256, 2, 8, 6, 4, false>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
             case 2: return gang_run<T, S, 256, 4, 8, 7, 2, false>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
             case 3: return gang_run<T, S, 512, 4, 8, 8, 2, true>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
-            case 4: return gang_run<T, S, 512, 6, 12, 8, 2, true>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
+            case 4: return gang_run<T, S, 512, 5, 10, 8, 2, true>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
+            case 5: return gang_run<T, S, 512, 6, 12, 8, 2, true>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
         }
     }
 }

@@ -55,16 +55,16 @@ def check_similarity(L, n, cplx):
 
 
 @pytest.mark.parametrize("cplx,n", [(False, n) for n in (64, 65, 128, 129, 200, 256, 257, 512, 513, 1024, 1025, 2048,
-                                                         2049, 3072, 3105)] +
-                         [(True, n) for n in (64, 65, 128, 129, 256, 257, 300, 512, 513, 1024, 1025, 1536, 1537, 2048,
-                                              2081)])
+                                                         2049, 2560, 2561, 3072, 3105)] +
+                         [(True, n) for n in (64, 65, 128, 129, 256, 257, 300, 512, 513, 1024, 1025, 1536, 1537, 1792, 1793,
+                                              2048, 2081)])
 def test_edges_of_the_shapes(L, cplx, n):
     announce("gang", cplx, n)
     check_similarity(L, n, cplx)
 
 
 @pytest.mark.parametrize("cplx", [False, True])
-@pytest.mark.parametrize("level,n", [(1, 1025), (1, 1700), (2, 129), (2, 333), (2, 1030)])
+@pytest.mark.parametrize("level,n", [(1, 1025), (1, 1700), (1, 2300), (2, 129), (2, 333), (2, 1030)])
 def test_gangs_that_leave(L, cplx, level, n):
     """The form in memory (level 1) and the single workgroup (level 2) do the
     columns of gangs that left."""
