@@ -241,8 +241,10 @@ def time_route(p, H, S, route, steps, warmup, stride, stream, graph=False, warm=
 def symv_roofline(prof, traffic):
     hemv_avg_us = 1e3 * prof.hemv_ms / max(1, prof.hemv_launches)
     hemv_gbs = prof.hemv_bytes / max(1e-12, prof.hemv_ms * 1e-3) / 1e9
-    return {"bound": "hbm", "kernel": "symv_kernel (trailing Hermitian matrix-vector product of the "
-                                      "one-stage tridiagonalisation)",
+    return {"bound": "hbm", "kernel": "trailing Hermitian matrix-vector products of the one-stage tridiagonalisation "
+                                      "(a sampled launch is a panel of 32 columns, trd_panel_kernel, for one matrix; "
+                                      "a column's symv_kernel for a batch); bytes: the lower triangle once per column, "
+                                      "of which a panel keeps a part on the chip",
             "achieved": hemv_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": hemv_gbs / PEAK_HBM_GBS,
             "traffic": traffic["bytes"] if traffic else None,
             "traffic_over_algorithmic": traffic["over_algorithmic"] if traffic else None,

@@ -268,6 +268,8 @@ ks_status ks_density_backward(ks_plan* plan, const double* eps, const void* C, c
  * e.g. the breakdown of Parts 2-1 .. 4 per SCF cycle).  With profiling enabled the
  * plan records HIP events on its stream around each phase below and around every
  * `stride`-th launch of the tridiagonalisation's trailing matrix-vector kernel
+ * (of the panels of columns that do these products, where one launch does a panel;
+ * orders whose trailing matrix stays in registers have none)
  * (the bandwidth-bound half of the eigensolver, Sec. 6).  Profiling adds a few
  * event records per phase; keep it off for plain timing. */
 enum {
@@ -282,7 +284,7 @@ typedef struct {
     double hemv_ms;           /* summed duration of the sampled kernel launches     */
     int64_t hemv_launches;    /* sampled launches                                   */
     double hemv_bytes;        /* their algorithmic bytes: the lower triangle of the  */
-                              /* trailing matrix, read once per launch              */
+                              /* trailing matrix, once per column of the launch     */
 } ks_profile;
 
 /* enable != 0 turns recording on (stride >= 1), 0 turns it off.  Host-only. */

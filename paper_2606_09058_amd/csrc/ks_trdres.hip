@@ -613,8 +613,8 @@ struct GangShape {
 constexpr int CHIP_CUS = 256;
 // us per column measured on an MI355X (the largest shape of each type keeps some
 // of its registers in scratch memory; the one below it takes over as soon as it can:
-// 2600 real 13.8 -> 11.5 ms, 2048 complex with its backward pass 26.8 -> 26.1); the two-launch column costs 12 to 15
-// (real) and 16 to 23 (complex) at these orders
+// 2600 real 13.8 -> 11.5 ms, 2048 complex with its backward pass 26.8 -> 26.1); the
+// two-launch column costs 12 to 15 (real) and 16 to 23 (complex) at these orders
 constexpr GangShape SHAPES_R[] = {{256, 5, 8, 2.0}, {512, 6, 16, 2.1}, {1024, 7, 64, 2.45}, {2048, 8, CHIP_CUS, 2.85},
                                   {2560, 8, CHIP_CUS, 3.7}, {3072, 8, CHIP_CUS, 8.3}};
 constexpr GangShape SHAPES_C[] = {{256, 5, 8, 2.5},   {512, 6, 32, 2.9},          {512, 4, 16, 4.8},
