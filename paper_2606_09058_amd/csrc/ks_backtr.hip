@@ -214,12 +214,13 @@ __device__ inline double fermi_count(double x) {
 // 1.5 us however few the eigenvalues.  The eigenvalues are therefore taken in
 // chunks of 64, of which only those within 40 kT of the point are looked at
 // (the others are full or empty, by their smallest and largest value): a lane
-// keeps what a wavefront has to know of one of its chunks.  Up to 64 chunks
+// keeps what a wavefront has to know of one of its chunks.  Up to 12 chunks
 // every wavefront has them all, and the sixteen count at the 15 inner points
 // of four halvings at once; beyond, the wavefronts share the chunks of one count.
 // (Against all eigenvalues at every halving: order 64 76 -> 21 us, 8 x 208
-// 230 -> 108, 1300 106 -> 70, 16 x 1300 800 -> 158.)
-constexpr int FERMI_CHUNKS = 64;
+// 230 -> 97, 1300 106 -> 50, 16 x 1300 800 -> 158.  The line at 12 chunks: with 21
+// and 32 of them in every wavefront 70 and 108 us, shared 50 and 97.)
+constexpr int FERMI_CHUNKS = 64, FERMI_FEW = 12;  // chunks in LDS, chunks in every wavefront
 __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const double* eps,
                                                      KWeights kw, double g, double ne, double kT,
                                                      int il, int iu, double* occ, double* mu_out,
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int per = (order + 63) / 64;  // chunks of a k-point
     const long nchunk = (long)batch * per;
-    const bool few = nchunk <= FERMI_CHUNKS, held = nchunk <= 16 * 64;
+    const bool few = nchunk <= FERMI_FEW, lds = nchunk <= FERMI_CHUNKS, held = nchunk <= 16 * 64;
     // chunk c of the wavefront: c itself, or c * 16 + wave
     auto chunk_id = [&](long c) { return few ? c : c * 16 + wave; };
     double mn = INFINITY, mx = -INFINITY;
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const
         const int num = min(64, (int)((bq + 1) * order - base));
         const bool in = lane < num;
         const double e = in ? eps[base + lane] : 0.0;
-        if (few && wave == (int)(c & 15)) se[id * 64 + lane] = in ? e : INFINITY;
+        if (few ? wave == (int)(c & 15) : lds) se[id * 64 + lane] = in ? e : INFINITY;
         const double a = wave_min(in ? e : INFINITY), z = wave_max(in ? e : -INFINITY);
         const bool nan = __any(e != e);  // such a chunk is neither full nor empty
         mn = fmin(mn, a);
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const
             cmin = nan ? -INFINITY : a;
             cmax = nan ? INFINITY : z;
             cw = g * kw.w[bq];
-            cbase = few ? id * 64 : base;
+            cbase = lds ? id * 64 : base;
             cnum = num;
         }
     }
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const
     hi += 50.0 * kT;
     __syncthreads();
     const double ikT = 1.0 / kT;
-    const double* src = few ? se : eps;
+    const double* src = lds ? se : eps;
     // the wavefront's chunks' electrons at x, in every lane
     auto count = [&](double x) {
         double cnt = 0.0;

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kT", [1e-4, 0.02, 0.5])
-@pytest.mark.parametrize("n,batch", [(1, 1), (2, 3), (63, 2), (64, 1), (65, 5), (64, 32), (128, 32), (129, 32), (4096, 1),
+@pytest.mark.parametrize("n,batch", [(1, 1), (2, 3), (63, 2), (64, 1), (65, 5), (64, 12), (65, 6), (64, 13), (64, 32), (128, 32), (129, 32), (4096, 1),
                                      (4097, 1), (1024, 63), (1024, 64)])
 def test_levels(n, batch, kT):
     """The electron count to 1e-12 and the width of the last bisection interval
