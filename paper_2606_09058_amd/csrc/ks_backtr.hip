@@ -192,16 +192,17 @@ void load_z(hipStream_t s, int n, int batch, int ncols, const double* Z, int c0,
 }
 
 // ---------------------------------------------------------------- Fermi level
-// 1 / (1 + e^x); 0 or 1 to 4e-18 beyond 40, without an exponential.
+// 1 / (1 + e^x); 1 to half a unit in the last place below -40, and 0 beyond the
+// smallest number, without an exponential.
 __device__ inline double fermi_F(double x) {
-    const double y = fabs(x);
-    if (y > 40.0) return x > 0.0 ? (y > 800.0 ? 0.0 : exp(-y)) : 1.0;
-    const double e = exp(-y), r = 1.0 / (1.0 + e);
-    return x > 0.0 ? e * r : r;
+    if (x < -40.0) return 1.0;
+    if (x > 800.0) return 0.0;
+    const double e = exp(-fabs(x));
+    return (x > 0.0 ? e : 1.0) / (1.0 + e);
 }
-// The same for the electron count alone, where 4e-18 of a state is nothing.
-__device__ inline double fermi_count(double x) {
-    if (x > 40.0) return 0.0;
+// The same for the electron count, where a state beyond `none` is nothing.
+__device__ inline double fermi_count(double x, double none) {
+    if (x > none) return 0.0;
     if (x < -40.0) return 1.0;
     const double e = exp(-fabs(x)), r = 1.0 / (1.0 + e);
     return x > 0.0 ? e * r : r;
@@ -212,9 +213,10 @@ __device__ inline double fermi_count(double x) {
 // 200 halvings), mu = midpoint; then occ, E_band and the window check.
 // A halving is a chain of exponentials, a sum over the workgroup and a barrier,
 // 1.5 us however few the eigenvalues.  The eigenvalues are therefore taken in
-// chunks of 64, of which only those within 40 kT of the point are looked at
-// (the others are full or empty, by their smallest and largest value): a lane
-// keeps what a wavefront has to know of one of its chunks.  Up to 12 chunks
+// chunks of 64, of which only those near the point are looked at: a chunk 40 kT below
+// it is full, and one beyond `none` = 44 + ln(states / electrons) is empty (all
+// such states together hold less than 1e-19 of the electrons asked for, however few
+// these are).  A lane keeps what a wavefront has to know of one of its chunks.  Up to 12 chunks
 // every wavefront has them all, and the sixteen count at the 15 inner points
 // of four halvings at once; beyond, the wavefronts share the chunks of one count.
 // (Against all eigenvalues at every halving: order 64 76 -> 21 us, 8 x 208
@@ -269,7 +271,10 @@ __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const
     lo -= 50.0 * kT;
     hi += 50.0 * kT;
     __syncthreads();
-    const double ikT = 1.0 / kT;
+    const double ikT = 1.0 / fmax(kT, 0x1p-1022);
+    double states = 0.0;
+    for (int b = 0; b < batch; ++b) states += g * kw.w[b] * order;
+    const double none = 44.0 + log(fmax(1.0, states / ne));
     const double* src = lds ? se : eps;
     // the wavefront's chunks' electrons at x, in every lane
     auto count = [&](double x) {
@@ -277,19 +282,19 @@ __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const
         if (held) {
             bool act = false;
             if ((cmax - x) * ikT < -40.0) cnt = cw * cnum;
-            else act = !((cmin - x) * ikT > 40.0);
+            else act = !((cmin - x) * ikT > none);
             unsigned long long mask = __ballot(act && cnum > 0);
             while (mask) {
                 const int l = __builtin_amdgcn_readfirstlane(__ffsll(mask) - 1);
                 mask &= mask - 1;
                 const long base = __builtin_amdgcn_readlane((int)cbase, l);
                 const int num = __builtin_amdgcn_readlane(cnum, l);
-                if (lane < num) cnt += lane_get(cw, l) * fermi_count((src[base + lane] - x) * ikT);
+                if (lane < num) cnt += lane_get(cw, l) * fermi_count((src[base + lane] - x) * ikT, none);
             }
         } else {
             for (int b = 0; b < batch; ++b) {
                 double sb = 0.0;
-                for (int i = t; i < order; i += 1024) sb += fermi_count((eps[(long)b * order + i] - x) * ikT);
+                for (int i = t; i < order; i += 1024) sb += fermi_count((eps[(long)b * order + i] - x) * ikT, none);
                 cnt += g * kw.w[b] * sb;
             }
         }
