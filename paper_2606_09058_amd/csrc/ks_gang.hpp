@@ -72,6 +72,19 @@ __device__ __forceinline__ void fma_(cplx& acc, cplx a, cplx b) {
     acc.y = fma(a.y, b.x, fma(a.x, b.y, acc.y));
 }
 
+// a += v u + p w.  The products are added up before they meet a, which is then
+// rounded once: rounded at every product, the entries of a matrix that stays in
+// registers through all its columns had twice (complex) and 1.5 times (real) the
+// error of one that takes 32 columns at a time.
+__device__ __forceinline__ void rank2_(double& a, double v, double u, double p, double w) { a += fma(p, w, v * u); }
+__device__ __forceinline__ void rank2_(cplx& a, cplx v, cplx u, cplx p, cplx w) {
+    cplx d = mk(v.x * u.x, v.x * u.y);
+    d.x = fma(-v.y, u.y, d.x);
+    d.y = fma(v.y, u.x, d.y);
+    fma_(d, p, w);
+    a = mk(a.x + d.x, a.y + d.y);
+}
+
 }  // namespace
 
 }  // namespace ks

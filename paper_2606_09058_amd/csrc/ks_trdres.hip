@@ -145,8 +145,7 @@ __global__ __launch_bounds__(64 * NW) void trd_wave_kernel(int n, int k0, const 
                 const T vr = vp[g][0][r], pr = vp[g][1][r];
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
-                    fma_(a[r][c], vr, ua[c]);
-                    fma_(a[r][c], pr, ta[c]);
+                    rank2_(a[r][c], vr, ua[c], pr, ta[c]);
                     fma_(acc[q], a[r][c], x[c]);
                 }
             }
@@ -322,8 +321,7 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
                     T y;
                     if constexpr (MEM) y = am[(long)(r * C + c) * NT];
                     else y = a[r][c];
-                    fma_(y, vr, ua[c]);
-                    fma_(y, pr, ta[c]);
+                    rank2_(y, vr, ua[c], pr, ta[c]);
                     fma_(acc[q], y, x[c]);
                     if constexpr (MEM) am[(long)(r * C + c) * NT] = y;
                     else a[r][c] = y;
@@ -472,8 +470,7 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
             T y;
             if constexpr (MEM) y = am[(long)(r * C + c) * NT];
             else y = a[r][c];
-            fma_(y, vr, ua[c]);
-            fma_(y, pr, ta[c]);
+            rank2_(y, vr, ua[c], pr, ta[c]);
             if (i >= kend && i < m && j >= kend && j <= i) put(&A[(long)i * lda + j], y);
         }
     }
