@@ -101,7 +101,7 @@ constexpr int PROF_HEMV = 100;  // tag of the sampled kernel
 // tridiagonalisation in registers (ks_trdres.hip), per matrix of a batch.
 constexpr int GANG_ORDER = 3072;    // largest order of a gang
 constexpr int GANG_STATE = 8;       // words of a matrix's state
-constexpr int GANG_CHIP_BATCH = 4;  // largest batch whose gangs take the whole chip in turn
+constexpr int GANG_CHIP_BATCH = 4;  // largest batch whose gangs take the whole chip, one matrix after the other
 template <typename T>
 struct GangWork {
     T* xp = nullptr;       // 3 slots of the products p = A v, one entry per row of a workgroup
@@ -110,6 +110,14 @@ struct GangWork {
     T* mem = nullptr;      // order^2 entries, the rows of a whole-chip gang that could not gather (one matrix)
     long sxp = 0, sxr = 0, smem = 0;  // strides between matrices
     int ncu = 0;                      // compute units the plan's stream may use
+    GangWork at(int z) const {        // that of matrix z alone
+        GangWork g = *this;
+        g.xp += z * sxp;
+        g.xr += z * sxr;
+        g.state += GANG_STATE * z;
+        if (g.mem) g.mem += z * smem;
+        return g;
+    }
 };
 
 template <typename T>

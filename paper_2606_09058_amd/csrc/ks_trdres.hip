@@ -653,7 +653,7 @@ int wave_order(int batch, int ncu) {
 
 template <typename T, typename S>
 void gang_columns(int shape, hipStream_t s, int n, int k0, int kend, int B, S* A, int lda, long sA, T* Vall, double* d,
-                  double* e, T* tau, GangWork<T>& gw, int* info) {
+                  double* e, T* tau, GangWork<T> gw, int* info) {
     if constexpr (is_cplx<T>::value) {
         switch (shape) {
             case 0: return gang_run<T, S, 256, 1, 8, 5, 4, false>(s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
@@ -745,7 +745,14 @@ void hetrd_resident(hipStream_t s, int n, int k0, S* A, int lda, long sA, int B,
             if (q >= 0 && gang_us(g[q], B, gw.ncu) <= 0.8 * gang_us(g[p], B, gw.ncu)) next = std::max(next, g[i].order);
         }
         const int kend = m - std::min(next, m - 1);
-        gang_columns<T, S>(p, s, n, k0, kend, B, A, lda, sA, Vall, d, e, tau, gw, info);
+        // gangs that take the whole chip: one matrix's launches behind the other's, so
+        // that each finds it free.  (In one launch one of them got it and the others'
+        // columns were done in memory: 2 x 3072 real 66.6 -> 21.3 ms, 47.1 with two
+        // launches per column; 4 x 2048 real 33.8 -> 15.0, 31.2.)
+        const int step = g[p].cus == CHIP_CUS ? 1 : B;
+        for (int z = 0; z < B; z += step)
+            gang_columns<T, S>(p, s, n, k0, kend, step, A + z * sA, lda, sA, Vall + (long)z * n * n, d + (long)z * n,
+                               e + (long)z * n, tau + (long)z * n, gw.at(z), info);
         k0 += kend;
     }
     const int m = n - k0;
