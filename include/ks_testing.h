@@ -63,7 +63,8 @@ int32_t ks_test_set_iteration_caps(int32_t leaf_sweeps, int32_t secular_iters);
  * thread enqueues from now on: 1 = those that take the whole GPU leave at once
  * as if their workgroups had not become resident together, so that their form
  * in memory does the columns; 2 = every gang does, so that one workgroup does
- * them; 0 = none (the default).  Host-only. */
+ * them; 3 = as 1, with the forms in memory on the fewest workgroups they take;
+ * 0 = none (the default).  Host-only. */
 int32_t ks_test_set_gang_leave(int32_t level);
 
 /* One v_mfma_f64_16x16x4_f64 where lane l feeds A[l%16][l/16] and B[l/16][l%16]

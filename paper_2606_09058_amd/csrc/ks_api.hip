@@ -1042,7 +1042,8 @@ ks_status ks_plan_create(const ks_plan_desc* d, ks_plan** out) {
     layout(d, p);
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) {
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1 ||
+        !(p->hr.gang.chip = p->hc.gang.chip = gang_chip())) {
         (void)hipFree(p->base);
         delete p;
         return KS_ERR_HIP;

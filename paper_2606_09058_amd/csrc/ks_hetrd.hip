@@ -766,6 +766,7 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
     int ng = 1;
     g[0] = {s, batch, A, d, e, tau, Vall, w};
     const int mres = resident_order<T>(batch, w.gang.ncu);
+    GangWork<T> gang = w.gang;
     if (w.side && batch >= 2 && n > mres) {
         const int B0 = (batch + 1) / 2;
         g[0].B = B0;
@@ -800,7 +801,8 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
             hipEvent_t e0 = smp ? w.prof->take() : nullptr;
             hipEvent_t e1 = smp ? w.prof->take() : nullptr;
             if (smp) (void)hipEventRecord(e0, s);
-            hetrd_panel<T, S>(s, n, k0, A, lda, d, e, tau, Vall, w.VW, w.WV, w.gang, w.info);
+            hetrd_panel<T, S>(s, n, k0, A, lda, d, e, tau, Vall, w.VW, w.WV, gang, w.info);
+            gang.fresh = false;
             if (smp) {
                 (void)hipEventRecord(e1, s);
                 double bytes = 0.0;
@@ -878,7 +880,7 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
     }
     // the rest in registers, the whole batch in one launch: its gangs share the
     // GPU (or follow each other) by themselves
-    hetrd_resident<T, S>(s, n, k0, A, lda, sA, batch, d, e, tau, Vall, w.gang, w.info);
+    hetrd_resident<T, S>(s, n, k0, A, lda, sA, batch, d, e, tau, Vall, gang, w.info);
 }
 
 

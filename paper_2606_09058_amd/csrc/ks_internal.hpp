@@ -106,8 +106,10 @@ template <typename T>
 struct GangWork {
     T* xp = nullptr;       // 3 slots of the products p = A v, one entry per row of a workgroup
     T* xr = nullptr;       // 3 slots of the raw row that is the next column
-    int* state = nullptr;  // 8 words: the gang's state, workgroups that have arrived
+    int* state = nullptr;  // GANG_STATE words: the gang's state, workgroups that have arrived, ...
     T* mem = nullptr;      // order^2 entries, the rows of a whole-chip gang that could not gather (one matrix)
+    int* chip = nullptr;   // the device's word for the gangs that take the whole chip, see ks_trdres.hip
+    bool fresh = true;     // no gang of this solve has been launched yet
     long sxp = 0, sxr = 0, smem = 0;  // strides between matrices
     int ncu = 0;                      // compute units the plan's stream may use
     GangWork at(int z) const {        // that of matrix z alone
@@ -282,8 +284,8 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
 // columns from k0 on of every matrix of a batch reduced that way (A's trailing
 // rows and columns k0.. up to date in the lower triangle; d, e, tau and the
 // columns k0.. of Vall as from hetrd).  A gang whose workgroups do not become
-// resident together leaves its columns to slower kernels behind it; a wait
-// inside a gang that gives up records KS_ERR_NO_CONVERGENCE with detail -4.
+// resident together leaves its columns to slower kernels behind it, which form the
+// same sums in the same order; a wait inside a gang that gives up records KS_ERR_NO_CONVERGENCE with detail -4.
 template <typename T>
 int resident_order(int batch, int ncu);
 template <typename T, typename S>
@@ -309,8 +311,13 @@ void gang_open(hipStream_t s, GangWork<T> gw, T* p, long words);
 template <typename T, typename S>
 void trd_single_panel(hipStream_t s, int n, int k0, int kend, S* A, int lda, T* Vall, double* d, double* e, T* tau,
                       T* VW, T* WV, GangWork<T> gw);
+// The device's word for the gangs that take the whole chip (null: no such symbol).
+int* gang_chip();
+// Workgroups of a form in memory that come if all do (few: those that always find room).
+int gang_half(int half, int few);
 // Test hook, for the launches of the calling thread: 1 = the gangs that take the
-// whole chip leave at once, 2 = every gang does, 0 = none.
+// whole chip leave at once, 2 = every gang does, 3 = as 1, with their forms in memory
+// on the fewest workgroups, 0 = none.
 void trd_set_leave(int level);
 
 // Tiles-per-workgroup candidates of the symmetric product for element type T,

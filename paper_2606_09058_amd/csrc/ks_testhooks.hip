@@ -162,7 +162,7 @@ int32_t ks_test_set_iteration_caps(int32_t leaf_sweeps, int32_t secular_iters) {
 }
 
 int32_t ks_test_set_gang_leave(int32_t level) {
-    if (level < 0 || level > 2) return KS_ERR_INVALID_ARG;
+    if (level < 0 || level > 3) return KS_ERR_INVALID_ARG;
     ks::trd_set_leave(level);
     return KS_OK;
 }

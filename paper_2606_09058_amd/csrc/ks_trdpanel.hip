@@ -33,8 +33,15 @@
 // 9984 complex 944 -> 773.
 //
 // Residency, the gate and what happens when the workgroups do not gather are
-// as in ks_trdres.hip: a form of 64 workgroups that does four blocks each and
-// keeps nothing, then one workgroup.
+// as in ks_trdres.hip: a form of 128 workgroups that does two blocks each (64 and four
+// where these are not free) and keeps nothing, but forms the same sums, then one
+// workgroup.  Whole tridiagonalisations with their panels in that form (two launches per
+// column): 6656 real 114 ms (144), 4160 complex 99 (109), 9984 complex 765 (727), 10000
+// real 442 (359); on 64 workgroups 179, 165, 1295 and 802.
+
+// Sums as they are written: the forms of a gang would give other bits if the compiler
+// chose for each which products it fuses.
+#pragma clang fp contract(off)
 #include "ks_gang.hpp"
 #include "ks_lanes.hpp"
 
@@ -54,7 +61,7 @@ constexpr int PS = PV - PB;                     // workgroups that add the share
 
 template <typename T, typename S>
 struct Panel {
-    int n, k0, jb, P;        // order, first column, columns, workgroups
+    int n, k0, jb;           // order, first column, columns
     int m, ro, rop, h, q;    // trailing order, rows of an owner (padded), of a block, block rows in use
     int lda;
     const S* A;              // at (k0, k0)
@@ -62,7 +69,7 @@ struct Panel {
     double *d, *e;
     T* tau;
     T *xb, *pb, *db, *sb, *vb, *hb;  // exchange: column, partial products, shares, sums, x^H A x, head rows
-    int* state;
+    int *state, *chip;
     int* info;
 };
 
@@ -121,7 +128,7 @@ __device__ __forceinline__ void poll(T (&v)[N], const T* const (&p)[N], int* sta
         if ((spin & 1023) == 1023) {
             const long long now = wall_clock64();
             if (t0 == 0) t0 = now;
-            if (now - t0 > WAIT_MS * TICKS) atomicCAS(&state[0], GANG_GO, GANG_FAILED);
+            if (now - t0 > WAIT_MS * TICKS) atomicExch(&state[0], GANG_FAILED);
             if (__hip_atomic_load(&state[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == GANG_FAILED) {
                 *sfail = 1;
                 break;
@@ -132,8 +139,10 @@ __device__ __forceinline__ void poll(T (&v)[N], const T* const (&p)[N], int* sta
 
 }  // namespace
 
-template <typename T, typename S, int C, int RR, int RL, bool MEM>
-__global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long long gate) {
+// RT: row slots of a wavefront that the form in registers keeps; from there on the
+// rows are read in turn (MEM reads them all, in the same order).
+template <typename T, typename S, int C, int RR, int RL, int RT, bool MEM>
+__global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long long gate, int half) {
     constexpr int H = 64 * C;                      // largest block
     constexpr int RK = RR + RL;                    // row slots of a wavefront that are kept (RL of them in LDS)
     constexpr bool ALL = PNW * RK >= H;            // every row
@@ -150,7 +159,7 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
     __shared__ S kept[RL > 0 ? RL * C : 1][PNT];
     __shared__ T svj[64], swj[64], sxe[64], sS[64], sH[64], sal, sz1;
     __shared__ double red[PNW];
-    __shared__ int sstate, sfail, scount;
+    __shared__ int sstate, sfail, scount, snum;
     int t = threadIdx.x, lane = t & 63;
     const int g = __builtin_amdgcn_readfirstlane(t >> 6);
     // what is derived from the lane is derived again in each phase: kept, it
@@ -160,24 +169,30 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
         asm volatile("" : "+v"(t));
         lane = t & 63;
     };
-    const int b = blockIdx.x, m = a.m, ro = a.ro, h = a.h, lda = a.lda;
-    int* state = a.state + (MEM ? 2 : 0);
-    if (MEM && state[-2] != GANG_LEFT) return;
+    const int m = a.m, ro = a.ro, h = a.h, lda = a.lda;
+    int b = blockIdx.x, P = PV;  // the workgroup's number, and how many there are
+    int* state = a.state + (MEM ? GS_MEM : 0);
+    if (MEM && state[GS_STATE - GS_MEM] != GANG_LEFT) return;
     if (t == 0) {
-        const long long t0 = wall_clock64();
-        if (atomicAdd(&state[1], 1) == a.P - 1) atomicCAS(&state[0], GANG_NONE, GANG_GO);
-        int st;
-        while ((st = __hip_atomic_load(&state[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == GANG_NONE) {
-            if (wall_clock64() - t0 >= gate) atomicCAS(&state[0], GANG_NONE, GANG_LEFT);
-        }
-        sstate = st;
         sfail = scount = 0;
+        if constexpr (MEM) {
+            snum = gather_in_memory(state, state[GS_CHIP - GS_MEM] ? half : PV / 4, PV / 4, gate, P);
+            sstate = P;
+        } else {
+            sstate = gather(state, PV, gate, a.chip);
+        }
     }
     for (int i = t; i < H + 64; i += PNT) sxr[i] = zero_<T>();
     if constexpr (!MEM)
         for (int i = t; i < NB * ROM; i += PNT) sV[i / ROM][i % ROM] = sW[i / ROM][i % ROM] = zero_<T>();
     __syncthreads();
-    if (sstate != GANG_GO) return;
+    if constexpr (MEM) {
+        b = __builtin_amdgcn_readfirstlane(snum);
+        P = __builtin_amdgcn_readfirstlane(sstate);
+        if (b >= P) return;
+    } else {
+        if (sstate != GANG_GO) return;
+    }
     T* party = szc;  // [PNW][64] each, in phase B
     T* partc = szc + PNW * 64;
     // partial products of an owner's row: block row s at offset s rop
@@ -233,7 +248,7 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
     const int rall = (h + PNW - 1) / PNW;  // row slots of a wavefront
 
     // ---- column k0
-    for (int v = b; v < PV; v += a.P) {
+    for (int v = b; v < PV; v += P) {
         if (g != 0) continue;
         const int i = v * ro + lane;
         const bool in = v < PO && lane < ro && i < m;
@@ -290,7 +305,7 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
         const int at1 = row_at(i1);
         bool asked = false;
         const T* X = a.xb + (long)xslot * m;
-        T* P = a.pb + slot * ps;
+        T* Pj = a.pb + slot * ps;
         T* Pp = a.pb + prev * ps;
         T* D = a.db + slot * ND * PV;
         T* Sm = a.sb + slot * PS * ND;
@@ -300,7 +315,7 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
         // ---------------- A
         fresh();
         if (!MEM) raw_column(b, i1);
-        for (int v = b; v < PV; v += a.P) {
+        for (int v = b; v < PV; v += P) {
             if (v >= PB) {  // sums of the owners' shares
                 constexpr int NU = (PV + PS * PNW - 1) / (PS * PNW), NC = is_cplx<T>::value ? (NU + 1) / 2 : NU;
                 const bool share = lane == DN || (lane & (NB - 1)) < j;
@@ -335,7 +350,7 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
             if (bI >= a.q) continue;
             // the rows that are not kept, from the last one in every other column:
             // what the column before read last is still in the memory-side cache
-            auto turn = [&](int r) { return (j & 1) && r < rall ? RK + rall - 1 - r : r; };
+            auto turn = [&](int r) { return (j & 1) && r >= RT && r < rall ? RT + rall - 1 - r : r; };
             S buf[2][SG][C];
             auto load = [&](int r, int p) {
 #pragma unroll
@@ -463,15 +478,15 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
                 if (bI == bJ) {
                     const T z = (zr + zs) + dx * x;
                     if (i >= i1 && i < m) {
-                        publish(P + atI + bI * a.rop, z);
+                        publish(Pj + atI + bI * a.rop, z);
                         va = re_(conj_(x) * z);
                     }
                 } else {
                     if (i >= i1 && i < m) {
-                        publish(P + atI + bJ * a.rop, zr);
+                        publish(Pj + atI + bJ * a.rop, zr);
                         va = 2.0 * re_(conj_(x) * zr);
                     }
-                    if (jj >= i1) publish(P + atJ + bI * a.rop, zs);
+                    if (jj >= i1) publish(Pj + atJ + bI * a.rop, zs);
                 }
             }
             va = lane_sum(va);
@@ -523,7 +538,7 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
             cs = lane_sum(cs);
             cr = lane_sum(cr);
         }
-        for (int v = b; v < PV; v += a.P) {
+        for (int v = b; v < PV; v += P) {
             fresh();
             const int i = v * ro + lane, r = min(i, m - 1);
             const bool in = v < PO && lane < ro && i < m && i >= i1;
@@ -534,18 +549,18 @@ __global__ __launch_bounds__(PNT, 2) void trd_panel_kernel(Panel<T, S> a, long l
 #pragma unroll
             for (int u = 0; u < 3; ++u) {
                 const int s = g + PNW * u;
-                p[u] = P + (min(v, PO - 1) * PQ + min(s, PQ - 1)) * a.rop + min(lane, ro - 1);
+                p[u] = Pj + (min(v, PO - 1) * PQ + min(s, PQ - 1)) * a.rop + min(lane, ro - 1);
                 x[u] = in && s < a.q ? peek(p[u]) : zero_<T>();
             }
             bool want = false;
-            p[3] = P;
+            p[3] = Pj;
             if (g >= 1 && g <= 4) {
                 const int f = (g - 1) * 64 + lane;
                 want = f < a.q * (a.q + 1) / 2;
                 p[3] = Vx + f;
             } else if (g == 5) {
                 want = lane < a.q;
-                p[3] = P + at1 + min(lane, PQ - 1) * a.rop;
+                p[3] = Pj + at1 + min(lane, PQ - 1) * a.rop;
             }
             x[3] = want ? peek(p[3]) : zero_<T>();
             // what the panel takes off A v and off the next column
@@ -702,12 +717,10 @@ long panel_words(int m, int rop) {
 }
 
 template <typename T, typename S, int C, int RR, int RL>
-void panel_run(hipStream_t s, const Panel<T, S>& a, long long gate, long long gate2) {
-    Panel<T, S> b = a;
-    b.P = PV;
-    hipLaunchKernelGGL((trd_panel_kernel<T, S, C, RR, RL, false>), dim3(PV), dim3(PNT), 0, s, b, gate);
-    b.P = PV / 4;
-    hipLaunchKernelGGL((trd_panel_kernel<T, S, C, 0, 0, true>), dim3(PV / 4), dim3(PNT), 0, s, b, gate2);
+void panel_run(hipStream_t s, const Panel<T, S>& a) {
+    hipLaunchKernelGGL((trd_panel_kernel<T, S, C, RR, RL, RR + RL, false>), dim3(PV), dim3(PNT), 0, s, a, gang_gate(1), 0);
+    hipLaunchKernelGGL((trd_panel_kernel<T, S, C, 0, 0, RR + RL, true>), dim3(PV / 2), dim3(PNT), 0, s, a, gang_gate(2),
+                       gang_half(PV / 2, PV / 4));
 }
 
 }  // namespace
@@ -726,7 +739,6 @@ void hetrd_panel(hipStream_t s, int n, int k0, S* A, int lda, double* d, double*
     a.n = n;
     a.k0 = k0;
     a.jb = NB;
-    a.P = PV;
     a.m = n - k0;
     a.ro = cdiv(a.m, PO);
     a.rop = cdiv(a.ro, 8) * 8;
@@ -740,6 +752,7 @@ void hetrd_panel(hipStream_t s, int n, int k0, S* A, int lda, double* d, double*
     a.e = e + k0;
     a.tau = tau + k0;
     a.state = gw.state;
+    a.chip = gw.chip;
     a.info = info;
     const long words = panel_words<T>(a.m, a.rop);
     T* p = gw.mem;
@@ -749,11 +762,10 @@ void hetrd_panel(hipStream_t s, int n, int k0, S* A, int lda, double* d, double*
     a.sb = a.db + 3L * ND * PV;
     a.vb = a.sb + 3 * PS * ND;
     a.hb = a.vb + 3 * PV;
-    const long long g1 = gang_gate(1), g2 = gang_gate(2);
     gang_open<T>(s, gw, p, words);
     const int c = cdiv(a.h, 64);
     constexpr bool cx = is_cplx<T>::value, lo = !std::is_same<T, S>::value;
-#define KS_PANEL(CC, RR_, RL_) panel_run<T, S, CC, RR_, RL_>(s, a, g1, g2)
+#define KS_PANEL(CC, RR_, RL_) panel_run<T, S, CC, RR_, RL_>(s, a)
     // rows in registers (what 256 hold beside x, the column sums and the rows on
     // their way) and in LDS
     if constexpr (!cx && !lo) {

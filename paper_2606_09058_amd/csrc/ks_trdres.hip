@@ -39,12 +39,16 @@
 //
 // A gang waits for its own workgroups, so all of them have to be resident.
 // They first count in; if they do not all arrive in time (other kernels hold
-// the compute units), the gang leaves without having touched the matrix, and
+// compute units), the gang leaves without having touched the matrix, and
 // a kernel launched behind it does the columns instead: the same gang with its
-// rows in memory (128 workgroups, 14 to 40 us per column) behind one that
-// takes the whole chip, one workgroup (trd_single_kernel) behind the others.
-// Waits inside a gang that is complete are bounded as well
+// rows in memory (on half the chip, or a quarter where that is not free either)
+// behind one that takes the whole chip, one workgroup (trd_single_kernel) behind
+// the others.  Waits inside a gang that is complete are bounded as well
 // (KS_ERR_NO_CONVERGENCE, detail -4).
+
+// Sums as they are written: the forms of a gang would give other bits if the compiler
+// chose for each which products it fuses.
+#pragma clang fp contract(off)
 #include "ks_gang.hpp"
 #include "ks_lanes.hpp"
 
@@ -120,7 +124,7 @@ __global__ __launch_bounds__(64 * NW) void trd_wave_kernel(int n, int k0, const 
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int j = lane + 64 * c;
-            nx += j > k1 ? abs2_(x[c]) : 0.0;
+            add_abs2(nx, pick(j > k1, x[c], zero_<T>()));
             xk = pick(c == (k1 >> 6), x[c], xk);
         }
         const double xn2 = lane_sum(nx);
@@ -173,11 +177,13 @@ __global__ __launch_bounds__(64 * NW) void trd_wave_kernel(int n, int k0, const 
         for (int c = 0; c < C; ++c) {
             const int j = lane + 64 * c;
             const bool in = j > k && j < m;
-            v[c] = j == k1 ? from_re<T>(1.0) : sc * x[c];
+            v[c] = pick(j == k1, from_re<T>(1.0), mul_(sc, x[c]));
             const T zj = zb[(j % NW) * R + j / NW];
             row[c] = in ? conj_(rb[j]) : zero_<T>();
-            p[c] = in ? sc * zj + c1 * row[c] : zero_<T>();
-            gs += re_(conj_(v[c]) * p[c]);
+            p[c] = mul_(c1, row[c]);
+            fma_(p[c], sc, zj);
+            p[c] = pick(in, p[c], zero_<T>());
+            add_dot(gs, v[c], p[c]);
             if (j % NW == g) {  // own rows: for the update, and the reflector's entries
                 vp[g][0][j / NW] = v[c];
                 vp[g][1][j / NW] = p[c];
@@ -190,10 +196,14 @@ __global__ __launch_bounds__(64 * NW) void trd_wave_kernel(int n, int k0, const 
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int j = lane + 64 * c;
-            const T w = tv * p[c] + alw * v[c];
-            ta[c] = -(tv * conj_(v[c]));
-            ua[c] = -(conj_(w) + alw * conj_(v[c]));
-            x[c] = j > k1 ? row[c] - (v[c] * w1 + w) : zero_<T>();
+            T w = mul_(tv, p[c]);
+            add_scaled(w, alw, v[c]);
+            ta[c] = -mul_(tv, conj_(v[c]));
+            ua[c] = -conj_(w);
+            add_scaled(ua[c], -alw, conj_(v[c]));
+            T y = w;
+            fma_(y, v[c], w1);
+            x[c] = pick(j > k1, row[c] - y, zero_<T>());
             if (j == k1 && g == 0) d[k1] = re_(row[c]) - 2.0 * re_(w1);
         }
     }
@@ -211,22 +221,26 @@ __global__ __launch_bounds__(64 * NW) void trd_wave_kernel(int n, int k0, const 
 // compute unit that a workgroup takes).  MEM: the rows live in memory instead
 // of registers, each thread's own entries where only it reaches them: the
 // form behind a gang that takes the whole chip, when that could not gather.
+// Its workgroups take half a compute unit each and all fit half the chip; where
+// even that is taken, half of them do the rows of two each.  Either way every
+// sum is formed as in registers, so the results are the same.
 template <typename T, typename S, int NT, int C, int R, int WPE, bool MEM>
 __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int kend, int lp, S* A, int lda, long sA,
                                                            T* Vall, double* d, double* e, T* taua, GangWork<T> gw,
-                                                           long long gate, int* info) {
-    constexpr int NW = NT / 64;
+                                                           long long gate, int half, int* info) {
+    constexpr int NW = NT / 64, QM = MEM ? 2 : 1;
     static_assert(R <= NT, "one thread per row");
     // rows summed at a time
     constexpr int RC = MEM || R % 8 == 4 || (is_cplx<T>::value && R * C >= 32) ? 4 : R <= 8 || is_cplx<T>::value ? 8 : 16;
     __shared__ double red1[NW], red2[NW];
     __shared__ T salpha, sp1;
-    __shared__ T sv[R], sp[R];  // v and p on the workgroup's own rows
-    __shared__ T rowred[NW][R];
-    __shared__ int sstate, sfail;
+    __shared__ T sv[QM][R], sp[QM][R];  // v and p on the workgroup's own rows
+    __shared__ T rowred[QM][NW][R];
+    __shared__ int sstate, sfail, snum;
     const int t = threadIdx.x, lane = t & 63, g = t >> 6;
-    const int P = 1 << lp, b = blockIdx.x, z = blockIdx.y;
+    const int P = 1 << lp, z = blockIdx.y;
     const int m = n - k0;
+    int b = blockIdx.x, np = P;  // the workgroup's number, and how many there are
     // the thread's columns jc[c]: entry t + NT c of the exchange buffers, in
     // the order (workgroup, slot) of the rows, so that a workgroup writes and a
     // wavefront reads whole cache lines (entries in the order of the columns,
@@ -234,44 +248,61 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
     int jc[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) jc[c] = (((t + NT * c) % R) << lp) + (t + NT * c) / R;
-    int* state = gw.state + GANG_STATE * z + (MEM ? 2 : 0);  // [0] state, [1] arrivals
-    if (MEM && state[-2] != GANG_LEFT) return;
+    int* state = gw.state + GANG_STATE * z + (MEM ? GS_MEM : 0);
+    if (MEM && state[GS_STATE - GS_MEM] != GANG_LEFT) return;
     if (t == 0) {
-        const long long t0 = wall_clock64();
-        if (atomicAdd(&state[1], 1) == P - 1) atomicCAS(&state[0], GANG_NONE, GANG_GO);
-        int st;
-        while ((st = __hip_atomic_load(&state[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == GANG_NONE) {
-            if (wall_clock64() - t0 >= gate) atomicCAS(&state[0], GANG_NONE, GANG_LEFT);
-        }
-        sstate = st;
         sfail = 0;
+        if constexpr (MEM) {
+            snum = gather_in_memory(state, state[GS_CHIP - GS_MEM] ? half : P / 2, P / 2, gate, np);
+            sstate = np;
+        } else {
+            sstate = gather(state, P, gate, gw.chip);
+        }
     }
-    if (t < R) sv[t] = sp[t] = zero_<T>();
+    if (t < R)
+        for (int q = 0; q < QM; ++q) sv[q][t] = sp[q][t] = zero_<T>();
     __syncthreads();
-    if (sstate != GANG_GO) return;
+    if constexpr (MEM) {
+        b = snum;
+        np = sstate;
+        if (b >= np) return;
+    } else {
+        if (sstate != GANG_GO) return;
+    }
+    // f(q, o) for the owners o of rows o, o + P, ... whose rows are this workgroup's
+    auto each = [&](auto&& f) {
+        if constexpr (MEM) {
+            for (int q = 0; b + q * np < P; ++q) f(q, b + q * np);
+        } else {
+            f(0, b);
+        }
+    };
     A += z * sA + (long)k0 * lda + k0;
     Vall += (long)z * n * n;
     d += (long)z * n + k0;
     e += (long)z * n + k0;
     taua += (long)z * n + k0;
-    zero_above<T>(n, k0, kend, Vall, (b + k0) & (P - 1), P, t, NT);
+    each([&](int, int o) { zero_above<T>(n, k0, kend, Vall, (o + k0) & (P - 1), P, t, NT); });
     T* V = Vall + (long)k0 * n + k0;
     T* xp = gw.xp + z * gw.sxp;
     T* xr = gw.xr + z * gw.sxr;
     const int slotn = NT * C;
     T a[MEM ? 1 : R][MEM ? 1 : C], x[C], ua[C], ta[C];
-    T* am = MEM ? gw.mem + z * gw.smem + (long)b * R * C * NT + t : nullptr;
+    auto rows = [&](int o) { return gw.mem + z * gw.smem + (long)o * R * C * NT + t; };
+    each([&](int, int o) {
+        T* am = MEM ? rows(o) : nullptr;
 #pragma unroll(MEM ? 1 : R)
-    for (int r = 0; r < R; ++r) {
-        if (r % 4 == 0) asm volatile("" ::: "memory");  // four rows' addresses and loads at a time
+        for (int r = 0; r < R; ++r) {
+            if (r % 4 == 0) asm volatile("" ::: "memory");  // four rows' addresses and loads at a time
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int i = b + P * r, j = jc[c];
-            const T q = i < m && j < m ? herm_entry<T, S>(A, lda, i, j) : zero_<T>();
-            if constexpr (MEM) am[(long)(r * C + c) * NT] = q;
-            else a[r][c] = q;
+            for (int c = 0; c < C; ++c) {
+                const int i = o + P * r, j = jc[c];
+                const T q = i < m && j < m ? herm_entry<T, S>(A, lda, i, j) : zero_<T>();
+                if constexpr (MEM) am[(long)(r * C + c) * NT] = q;
+                else a[r][c] = q;
+            }
         }
-    }
+    });
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const int j = jc[c];
@@ -279,13 +310,18 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
         ua[c] = ta[c] = zero_<T>();
     }
     if (b == 0 && t == 0) d[0] = re_(widen(A[0]));
-    // the one of the thread's columns that is a row of this workgroup (entries
-    // b R .. b R + R - 1), its row's slot, and where its reflector entries go
-    int co = -1;
+    // the one of the thread's columns that is a row of owner o (entries o R ..
+    // o R + R - 1), its row's slot, and where its reflector entries go
+    auto mine = [&](int o, int& co, int& ro, int& jo) {
+        co = -1;
 #pragma unroll
-    for (int c = 0; c < C; ++c)
-        if ((t + NT * c) / R == b) co = c;
-    const int ro = (t + NT * max(co, 0)) % R, jo = co < 0 ? m : b + (ro << lp);
+        for (int c = 0; c < C; ++c)
+            if ((t + NT * c) / R == o) co = c;
+        ro = (t + NT * max(co, 0)) % R;
+        jo = co < 0 ? m : o + (ro << lp);
+    };
+    int co = -1, ro = 0, jo = m;
+    if (!MEM) mine(b, co, ro, jo);
     T* Vo = V + (long)min(jo, m - 1) * n;
     const T* xpt = xp + t;
     const T* xrt = xr + t;
@@ -294,69 +330,73 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
     do {
         const int k1 = k + 1, b1 = k1 & (P - 1), r1 = k1 >> lp;  // row k1: workgroup and slot,
         const int e1 = b1 * R + r1, c1e = e1 / NT, t1 = e1 % NT;   // column k1: entry, the thread's column, thread
-        const bool own = b1 == b, is1 = t == t1;
+        const bool is1 = t == t1;
         double nx = 0.0;
         T x1 = x[0];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            nx += jc[c] > k1 ? abs2_(x[c]) : 0.0;
+            add_abs2(nx, pick(jc[c] > k1, x[c], zero_<T>()));
             x1 = pick(c == c1e, x[c], x1);
         }
         if (is1) salpha = x1;
+        each([&](int qo, int o) {
+            T* am = MEM ? rows(o) : nullptr;
 #pragma unroll(MEM ? 1 : R)
-        for (int r0 = 0; r0 < R; r0 += RC) {
-            if (((r0 + RC) << lp) <= k1) continue;  // every row of these slots is done (uniform)
-            T acc[RC];
-#pragma unroll
-            for (int q = 0; q < RC; ++q) {
-                const int r = r0 + q;
-                acc[q] = zero_<T>();
-                if (r >= R) continue;
-                // (keeps the LDS reads of later rows behind: all at once they
-                // would take the registers of the matrix)
-                if (q % (is_cplx<T>::value ? 2 : 4) == 0) asm volatile("" ::: "memory");
-                const T vr = sv[r], pr = sp[r];
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    T y;
-                    if constexpr (MEM) y = am[(long)(r * C + c) * NT];
-                    else y = a[r][c];
-                    rank2_(y, vr, ua[c], pr, ta[c]);
-                    fma_(acc[q], y, x[c]);
-                    if constexpr (MEM) am[(long)(r * C + c) * NT] = y;
-                    else a[r][c] = y;
-                }
-            }
-            if (own && r1 >= r0 && r1 < r0 + RC) {
+            for (int r0 = 0; r0 < R; r0 += RC) {
+                if (((r0 + RC) << lp) <= k1) continue;  // every row of these slots is done (uniform)
+                T acc[RC];
 #pragma unroll
                 for (int q = 0; q < RC; ++q) {
-                    if (r0 + q >= R || r1 != r0 + q) continue;
+                    const int r = r0 + q;
+                    acc[q] = zero_<T>();
+                    if (r >= R) continue;
+                    // (keeps the LDS reads of later rows behind: all at once they
+                    // would take the registers of the matrix)
+                    if (q % (is_cplx<T>::value ? 2 : 4) == 0) asm volatile("" ::: "memory");
+                    const T vr = sv[qo][r], pr = sp[qo][r];
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
-                        const int j = jc[c];
-                        if (j > k && j < m) {
-                            if constexpr (MEM) publish(&xr[slot * slotn + t + NT * c], am[(long)((r0 + q) * C + c) * NT]);
-                            else publish(&xr[slot * slotn + t + NT * c], a[r0 + q < R ? r0 + q : 0][c]);
+                        T y;
+                        if constexpr (MEM) y = am[(long)(r * C + c) * NT];
+                        else y = a[r][c];
+                        rank2_(y, vr, ua[c], pr, ta[c]);
+                        fma_(acc[q], y, x[c]);
+                        if constexpr (MEM) am[(long)(r * C + c) * NT] = y;
+                        else a[r][c] = y;
+                    }
+                }
+                if (b1 == o && r1 >= r0 && r1 < r0 + RC) {
+#pragma unroll
+                    for (int q = 0; q < RC; ++q) {
+                        if (r0 + q >= R || r1 != r0 + q) continue;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            const int j = jc[c];
+                            if (j > k && j < m) {
+                                if constexpr (MEM) publish(&xr[slot * slotn + t + NT * c], am[(long)((r0 + q) * C + c) * NT]);
+                                else publish(&xr[slot * slotn + t + NT * c], a[r0 + q < R ? r0 + q : 0][c]);
+                            }
                         }
                     }
                 }
+                const T s = lane_sums(acc, lane);
+                constexpr int LPR = 64 / RC;
+                if (lane % LPR == 0 && r0 + lane / LPR < R) rowred[qo][g][r0 + lane / LPR] = s;
             }
-            const T s = lane_sums(acc, lane);
-            constexpr int LPR = 64 / RC;
-            if (lane % LPR == 0 && r0 + lane / LPR < R) rowred[g][r0 + lane / LPR] = s;
-        }
+        });
         nx = lane_sum(nx);
         if (lane == 0) red1[g] = nx;
         // this workgroup's resets of the slot of column k+1 are in memory
         // before it publishes column k (they were issued a column ago)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (t < R) {
-            T s = zero_<T>();
+        if (t < R)
+            each([&](int qo, int o) {
+                T s = zero_<T>();
 #pragma unroll
-            for (int q = 0; q < NW; ++q) s += rowred[q][t];
-            publish(&xp[slot * slotn + b * R + t], s);
-        }
+                for (int q = 0; q < NW; ++q) s += rowred[qo][q][t];
+                publish(&xp[slot * slotn + o * R + t], s);
+            });
         // the reflector, while the products are on their way
         double xn2 = 0.0;
 #pragma unroll
@@ -370,11 +410,19 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int j = jc[c];
-            v[c] = pick(j == k1, from_re<T>(1.0), sc * x[c]);
+            v[c] = pick(j == k1, from_re<T>(1.0), mul_(sc, x[c]));
             vo = pick(c == co, v[c], vo);
             p[c] = row[c] = j > k && j < m ? empty_<T>() : zero_<T>();
         }
-        if (jo > k && jo < m) Vo[k] = vo;
+        if constexpr (MEM)
+            each([&](int, int o) {
+                mine(o, co, ro, jo);
+                T x = zero_<T>();
+#pragma unroll
+                for (int c = 0; c < C; ++c) x = pick(c == co, v[c], x);
+                if (jo > k && jo < m) V[(long)jo * n + k] = x;
+            });
+        else if (jo > k && jo < m) Vo[k] = vo;
         if (b == 0 && t == 0) {
             e[k] = beta;
             taua[k] = tv;
@@ -397,7 +445,7 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
                 if ((spin & 1023) == 1023) {
                     const long long now = wall_clock64();
                     if (t0 == 0) t0 = now;
-                    if (now - t0 > WAIT_MS * TICKS) atomicCAS(&state[0], GANG_GO, GANG_FAILED);
+                    if (now - t0 > WAIT_MS * TICKS) atomicExch(&state[0], GANG_FAILED);
                     if (__hip_atomic_load(&state[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == GANG_FAILED) {
                         sfail = 1;
                         break;
@@ -410,16 +458,32 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             row[c] = conj_(row[c]);
-            p[c] = sc * p[c] + c1 * row[c];  // A v = s A x + c a_{k+1}
-            gs += re_(conj_(v[c]) * p[c]);
+            const T z = p[c];  // A v = s A x + c a_{k+1}
+            p[c] = mul_(c1, row[c]);
+            fma_(p[c], sc, z);
+            add_dot(gs, v[c], p[c]);
             p1 = pick(c == c1e, p[c], p1);
             row1 = pick(c == c1e, row[c], row1);
             po = pick(c == co, p[c], po);
         }
         if (is1) sp1 = p1;
-        if (co >= 0) {
-            sv[ro] = vo;
-            sp[ro] = po;
+        if constexpr (MEM) {
+            each([&](int qo, int o) {
+                mine(o, co, ro, jo);
+                T x = zero_<T>(), y = x;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    x = pick(c == co, v[c], x);
+                    y = pick(c == co, p[c], y);
+                }
+                if (co >= 0) {
+                    sv[qo][ro] = x;
+                    sp[qo][ro] = y;
+                }
+            });
+        } else if (co >= 0) {
+            sv[0][ro] = vo;
+            sp[0][ro] = po;
         }
         gs = lane_sum(gs);
         if (lane == 0) red2[g] = gs;
@@ -429,16 +493,17 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
             return;
         }
         // column k's entries have all been read here, so column k-1's are free
-        if (k > 0) {
-            if (t < R) empty_out(&xp[prev * slotn + b * R + t]);
-            if ((k & (P - 1)) == b) {
+        if (k > 0)
+            each([&](int, int o) {
+                if (t < R) empty_out(&xp[prev * slotn + o * R + t]);
+                if ((k & (P - 1)) == o) {
 #pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    const int j = jc[c];
-                    if (j > k - 1 && j < m) empty_out(&xr[prev * slotn + t + NT * c]);
+                    for (int c = 0; c < C; ++c) {
+                        const int j = jc[c];
+                        if (j > k - 1 && j < m) empty_out(&xr[prev * slotn + t + NT * c]);
+                    }
                 }
-            }
-        }
+            });
         prev = slot;
         slot = slot == 2 ? 0 : slot + 1;
         double gr = 0.0;
@@ -449,36 +514,53 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int j = jc[c];
-            const T w = tv * p[c] + alw * v[c];
+            T w = mul_(tv, p[c]);
+            add_scaled(w, alw, v[c]);
             // A -= v w^H + w v^H with w_i = tau p_i + alw v_i on the own rows:
             // v_i (conj(w_j) + alw conj(v_j)) + p_i tau conj(v_j)
-            ta[c] = -(tv * conj_(v[c]));
-            ua[c] = -(conj_(w) + alw * conj_(v[c]));
-            x[c] = pick(j > k1, row[c] - (v[c] * w1 + w), zero_<T>());
+            ta[c] = -mul_(tv, conj_(v[c]));
+            ua[c] = -conj_(w);
+            add_scaled(ua[c], -alw, conj_(v[c]));
+            T y = w;
+            fma_(y, v[c], w1);
+            x[c] = pick(j > k1, row[c] - y, zero_<T>());
         }
         if (b == 0 && is1) d[k1] = re_(row1) - 2.0 * re_(w1);
     } while (++k < kend);
     if (kend >= m - 1) return;
+    each([&](int qo, int o) {
+        T* am = MEM ? rows(o) : nullptr;
 #pragma unroll(MEM ? 1 : R)
-    for (int r = 0; r < R; ++r) {
-        const int i = b + (r << lp);
-        asm volatile("" ::: "memory");
-        const T vr = sv[r], pr = sp[r];
+        for (int r = 0; r < R; ++r) {
+            const int i = o + (r << lp);
+            asm volatile("" ::: "memory");
+            const T vr = sv[qo][r], pr = sp[qo][r];
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int j = jc[c];
-            T y;
-            if constexpr (MEM) y = am[(long)(r * C + c) * NT];
-            else y = a[r][c];
-            rank2_(y, vr, ua[c], pr, ta[c]);
-            if (i >= kend && i < m && j >= kend && j <= i) put(&A[(long)i * lda + j], y);
+            for (int c = 0; c < C; ++c) {
+                const int j = jc[c];
+                T y;
+                if constexpr (MEM) y = am[(long)(r * C + c) * NT];
+                else y = a[r][c];
+                rank2_(y, vr, ua[c], pr, ta[c]);
+                if (i >= kend && i < m && j >= kend && j <= i) put(&A[(long)i * lda + j], y);
+            }
         }
-    }
+    });
 }
 
-// The whole-chip gangs of a device take turns: a gang that finds another one at
-// work leaves at once.
+// The whole-chip gangs of a device take turns: 0 = free, 1 = taken, 2 = by a gang whose
+// workgroups have gathered.  Before a gang its init kernel waits for its turn, bounded by
+// TURN_MS, but only TURN_US while the chip is taken and not gathered: the gang that
+// took it may need the compute unit that the wait itself is on.  Who has to go without
+// takes a quarter of the chip.  (Two solves of order 6656 on two streams: 319 ms when a gang
+// that found the chip taken left at once, 251 with the wait; 290 with two launches per column.)
 __device__ int g_chip = 0;
+constexpr long long TURN_US = 200, TURN_MS = 20;
+// After a panel that could not gather its workgroups, so many panels leave at once
+// before one waits for them again, doubled up to the most: what holds a compute
+// unit for longer than a gang waits (CHIP_GATE_MS) holds it for many panels.  (The gangs of
+// the last columns are few and long, and always wait.)
+constexpr int SKIP_FIRST = 4, SKIP_MOST = 32;
 
 // Before a gang: its buffers empty (those of a panel: words entries at p), its
 // state cleared, the chip taken if it needs that.
@@ -493,12 +575,38 @@ __global__ void gang_init_kernel(GangWork<T> gw, int slotn, int chip, T* p, long
     }
     if (i == 0) {
         int* state = gw.state + GANG_STATE * z;
-        const bool got = chip && atomicCAS(&g_chip, 0, 1) == 0;
-        state[0] = chip && !got ? GANG_LEFT : GANG_NONE;
-        state[1] = 0;
-        state[2] = GANG_NONE;
-        state[3] = 0;
-        state[4] = got;
+        int skip = 0, next = 0;
+        if (!gw.fresh) {
+            skip = state[GS_SKIP];
+            next = state[GS_SKIP_NEXT];
+            if (state[GS_TRIED]) {
+                next = state[GS_STATE] != GANG_LEFT ? 0 : next ? min(2 * next, SKIP_MOST) : SKIP_FIRST;
+                skip = next;
+            }
+        }
+        bool got = false;
+        if (chip) {
+            const long long t0 = wall_clock64();
+            long long t1 = t0;  // since when the chip has been taken and not gathered
+            for (;;) {
+                const int was = atomicCAS(gw.chip, 0, 1);
+                const long long now = wall_clock64();
+                got = was == 0;
+                if (was == 2) t1 = now;
+                if (got || now - t1 >= TURN_US * TICKS / 1000 || now - t0 >= TURN_MS * TICKS) break;
+                __builtin_amdgcn_s_sleep(8);
+            }
+        }
+        const bool panel = words > 0, tries = got && !(panel && skip > 0);
+        if (panel && skip > 0) --skip;
+        state[GS_STATE] = chip && !tries ? GANG_LEFT : GANG_NONE;
+        state[GS_ARRIVED] = 0;
+        state[GS_MEM + GS_STATE] = GANG_NONE;
+        state[GS_MEM + GS_ARRIVED] = 0;
+        state[GS_CHIP] = got;
+        state[GS_SKIP] = skip;
+        state[GS_SKIP_NEXT] = next;
+        state[GS_TRIED] = tries;
     }
 }
 
@@ -515,8 +623,8 @@ __global__ __launch_bounds__(1024) void trd_single_kernel(int n, int k0, int ken
     __shared__ double red[16];
     const int t = threadIdx.x, NT = blockDim.x, z = blockIdx.x, m = n - k0;
     const int* state = gw.state + GANG_STATE * z;
-    if (t == 0 && state[4]) atomicExch(&g_chip, 0);
-    if (state[0] != GANG_LEFT || (mem && state[2] != GANG_LEFT)) return;
+    if (t == 0 && state[GS_CHIP]) atomicExch(gw.chip, 0);
+    if (state[GS_STATE] != GANG_LEFT || (mem && state[GS_MEM + GS_STATE] != GANG_LEFT)) return;
     A += z * sA + (long)k0 * lda + k0;
     Vall += (long)z * n * n;
     d += (long)z * n + k0;
@@ -582,17 +690,14 @@ template <typename T, typename S, int NT, int C, int R, int LP, int WPE, bool CH
 void gang_run(hipStream_t s, int n, int k0, int kend, int B, S* A, int lda, long sA, T* Vall, double* d, double* e,
               T* tau, GangWork<T>& gw, int* info) {
     static_assert(NT * C == R << LP && NT * C <= GANG_ORDER, "columns");
-    const long long gate = (g_leave > (CHIP ? 0 : 1)) ? 0 : (CHIP ? CHIP_GATE_MS : GATE_MS) * TICKS;
+    const long long gate = CHIP ? gang_gate(1) : gang_gate(2);
     hipLaunchKernelGGL((gang_init_kernel<T>), dim3(cdiv(3 * NT * C, 256), B), dim3(256), 0, s, gw, NT * C, (int)CHIP,
                        (T*)nullptr, 0L);
     hipLaunchKernelGGL((trd_gang_kernel<T, S, NT, C, R, WPE, false>), dim3(1 << LP, B), dim3(NT), 0, s, n, k0, kend,
-                       LP, A, lda, sA, Vall, d, e, tau, gw, gate, info);
-    if constexpr (CHIP) {
-        // a quarter of the chip: 128 workgroups of half a compute unit
-        const long long g2 = (g_leave > 1 ? 0 : GATE_MS) * TICKS;
-        hipLaunchKernelGGL((trd_gang_kernel<T, S, NT, C, (R << LP) / 128, 4, true>), dim3(128, B), dim3(NT), 0, s, n, k0,
-                           kend, 7, A, lda, sA, Vall, d, e, tau, gw, g2, info);
-    }
+                       LP, A, lda, sA, Vall, d, e, tau, gw, gate, 0, info);
+    if constexpr (CHIP)
+        hipLaunchKernelGGL((trd_gang_kernel<T, S, NT, C, R, 4, true>), dim3(1 << LP, B), dim3(NT), 0, s, n, k0, kend,
+                           LP, A, lda, sA, Vall, d, e, tau, gw, gang_gate(2), gang_half(1 << LP, 1 << (LP - 1)), info);
     hipLaunchKernelGGL((trd_single_kernel<T, S>), dim3(B), dim3(1024), 0, s, n, k0, kend, A, lda, sA, Vall, d, e, tau,
                        gw, (int)CHIP, gw.xr, gw.sxr, (T*)nullptr, (T*)nullptr);
 }
@@ -602,7 +707,7 @@ void gang_run(hipStream_t s, int n, int k0, int kend, int B, S* A, int lda, long
 // one matrix of that order, and whether it takes more than a quarter of the
 // chip.  HIP runs at most four kernels of a process at once (its hardware
 // queues), so gangs of a quarter always find room beside each other; a larger
-// one takes turns (g_chip) and has its form in memory for when it cannot.
+// one takes turns (GangWork::chip) and has its form in memory for when it cannot.
 struct GangShape {
     int order, lp, cus;
     double us;
@@ -680,7 +785,16 @@ void gang_columns(int shape, hipStream_t s, int n, int k0, int kend, int B, S* A
 
 void trd_set_leave(int level) { g_leave = level; }
 
-long long gang_gate(int form) { return g_leave >= form ? 0 : (form == 1 ? CHIP_GATE_MS : GATE_MS) * TICKS; }
+int* gang_chip() {
+    void* p = nullptr;
+    return hipGetSymbolAddress(&p, HIP_SYMBOL(g_chip)) == hipSuccess ? (int*)p : nullptr;
+}
+
+long long gang_gate(int form) {
+    if (form == 1) return g_leave ? 0 : CHIP_GATE_MS * TICKS;
+    return g_leave == 2 ? 0 : GATE_MS * TICKS;
+}
+int gang_half(int half, int few) { return g_leave == 3 ? few : half; }
 
 template <typename T>
 void gang_open(hipStream_t s, GangWork<T> gw, T* p, long words) {
@@ -753,6 +867,7 @@ void hetrd_resident(hipStream_t s, int n, int k0, S* A, int lda, long sA, int B,
         for (int z = 0; z < B; z += step)
             gang_columns<T, S>(p, s, n, k0, kend, step, A + z * sA, lda, sA, Vall + (long)z * n * n, d + (long)z * n,
                                e + (long)z * n, tau + (long)z * n, gw.at(z), info);
+        gw.fresh = false;
         k0 += kend;
     }
     const int m = n - k0;
