@@ -307,7 +307,8 @@ ks_status ks_plan_get_profile(ks_plan* plan, ks_profile* out);
  * Back-transform and GEMM tiles: backtr_block is the number of reflectors per
  * compact-WY block of the back-transform (128 or 256) and gemm_big_min_k the
  * smallest inner dimension for which a large product takes the 128 x 128
- * tiles (KS_TUNE_NEVER: never, 64 x 64 tiles only).  backtr_ms[b][g] is the
+ * tiles (KS_TUNE_NEVER: never, 64 x 64 tiles only; the default 256 means 128
+ * for the block updates of a complex back-transform).  backtr_ms[b][g] is the
  * time of one back-transform of all eigenvectors with backtr_block = 128 << b
  * and gemm_big_min_k = 256 (g = 0) or KS_TUNE_NEVER (g = 1).
  *

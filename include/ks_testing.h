@@ -59,6 +59,10 @@ int32_t ks_test_he2hb(int32_t dtype, int32_t n, void* A, const double* X, int32_
  * lets a test drive that failure path with ordinary inputs. */
 int32_t ks_test_set_iteration_caps(int32_t leaf_sweeps, int32_t secular_iters);
 
+/* Products that took the large tiles, of those that the calling thread has
+ * enqueued so far.  Host-only. */
+int64_t ks_test_big_gemms(void);
+
 /* Gangs of workgroups of the tridiagonalisation, for the solves that the calling
  * thread enqueues from now on: 1 = those that take the whole GPU leave at once
  * as if their workgroups had not become resident together, so that their form

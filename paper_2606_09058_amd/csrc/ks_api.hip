@@ -929,7 +929,7 @@ ks_status tune_backtr(ks_plan* p) {
     float best = 3.0e38f;
     for (int bi = 0; bi < 2; ++bi)
         for (int gi = 0; gi < 2; ++gi) {
-            const int bt = 128 << bi, gk = gi ? KS_TUNE_NEVER : 256;
+            const int bt = 128 << bi, gk = gi ? KS_TUNE_NEVER : GEMM_BIG_MIN_K;
             set_backtr_block(w, order, bt);
             GemmPolicy gp(gk);
             const float t = time_min(p->s, 2, [&]() {
@@ -1088,7 +1088,7 @@ ks_status ks_plan_create(const ks_plan_desc* d, ks_plan** out) {
     p->tuning.seg_first[0] = 0;
     p->tuning.seg_tiles[0] = HETRD_SCH;
     p->tuning.backtr_block = backtr_block(p->order);
-    p->tuning.gemm_big_min_k = 256;
+    p->tuning.gemm_big_min_k = GEMM_BIG_MIN_K;
     if (d->flags & KS_PLAN_AUTOTUNE) {
         ks_tuning& tu = p->tuning;
         const long sA = (long)p->order * p->order;

@@ -165,8 +165,10 @@ void backtransform_q(hipStream_t s, int n, int batch, const T* Vall, int ncols, 
     if (nref <= 0 || ncols <= 0) return;
     int nblk = cdiv(nref, bt);
     // complex rank updates by 128 reflectors gain from the large tiles where there are
-    // enough of them (16 x 1300: 3.1 -> 2.6 ms)
-    GemmPolicy pol(std::is_same<T, cplx>::value ? std::min(128, gemm_big_min_k()) : gemm_big_min_k());
+    // enough of them (16 x 1300: 3.1 -> 2.6 ms): the threshold without tuning means 128
+    // for them, any other is the caller's
+    const int big = gemm_big_min_k();
+    GemmPolicy pol(std::is_same<T, cplx>::value && big == GEMM_BIG_MIN_K ? 128 : big);
     // Q X applies the blocks last to first; Q^H X = (H_{n-2}^H ... H_0^H) X applies them first to last
     for (int q = 0; q < nblk; ++q) {
         const int b = adjoint ? q : nblk - 1 - q;

@@ -365,6 +365,8 @@ constexpr int BIG_MIN_K = 256;
 static thread_local int g_big_min_k = BIG_MIN_K;
 void gemm_set_big_min_k(int k) { g_big_min_k = k; }
 int gemm_big_min_k() { return g_big_min_k; }
+static thread_local long g_big_launches = 0;
+long gemm_big_launches() { return g_big_launches; }
 // Output tiles of BM x BN (128 x 128; 64 x 64 for FP64 complex) with one
 // wave tile of BM/2 x BN/2 per wavefront (2 x 2 wavefronts), so that each k
 // step feeds (BM/32)(BN/32) MFMA blocks per wavefront per operand fragment
@@ -722,6 +724,7 @@ static void launch(hipStream_t s, int m, int n, int k, double alpha, const T* A,
     // FP32 gains from large tiles at one round of workgroups, FP64 from two
     const long min_tiles = (sizeof(T) == 4 || std::is_same<T, cplx32>::value) ? BIG_MIN_TILES : 2 * BIG_MIN_TILES;
     if (!kscale && k >= g_big_min_k && big_tiles >= min_tiles) {
+        ++g_big_launches;
         dim3 grid(cdiv(n, BBN), cdiv(m, BBM), batch);
         hipLaunchKernelGGL((gemm_big_kernel<T, OPA, OPB>), grid, dim3(256), 0, s, m, n, k, alpha, A, lda, sa, B,
                            ldb, sb, beta, C, ldc, sc, (int)uplo, kdev, (int)tri);

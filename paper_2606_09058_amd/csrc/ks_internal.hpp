@@ -28,6 +28,8 @@ constexpr int DC_LEAF_MIN = 16;  // smallest leaf the autotuner tries (the works
 // the launches the calling thread enqueues; GemmPolicy sets it for a scope.
 void gemm_set_big_min_k(int k);
 int gemm_big_min_k();
+long gemm_big_launches();  // large-tile products that the calling thread has enqueued (test hook)
+constexpr int GEMM_BIG_MIN_K = 256;  // a plan's threshold without tuning
 struct GemmPolicy {
     int prev;
     explicit GemmPolicy(int k) : prev(gemm_big_min_k()) { gemm_set_big_min_k(k); }

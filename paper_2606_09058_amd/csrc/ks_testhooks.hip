@@ -161,6 +161,8 @@ int32_t ks_test_set_iteration_caps(int32_t leaf_sweeps, int32_t secular_iters) {
     return KS_OK;
 }
 
+int64_t ks_test_big_gemms(void) { return ks::gemm_big_launches(); }
+
 int32_t ks_test_set_gang_leave(int32_t level) {
     if (level < 0 || level > 3) return KS_ERR_INVALID_ARG;
     ks::trd_set_leave(level);
