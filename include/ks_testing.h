@@ -10,7 +10,7 @@
 #ifndef KS_TESTING_H
 #define KS_TESTING_H
 
-#include <stdint.h>
+#include "ks.h"
 
 #ifdef __cplusplus
 extern "C" {
@@ -58,6 +58,10 @@ int32_t ks_test_he2hb(int32_t dtype, int32_t n, void* A, const double* X, int32_
  * word and finishes normally (its outputs are then undefined).  Host-only; it
  * lets a test drive that failure path with ordinary inputs. */
 int32_t ks_test_set_iteration_caps(int32_t leaf_sweeps, int32_t secular_iters);
+
+/* Edges of the plan's captured launch sequence (KS_PLAN_GRAPH) beyond those of a
+ * chain of its nodes: 0 = every launch follows the one before.  Host-only. */
+int32_t ks_test_graph_forks(ks_plan* plan, int32_t* forks);
 
 /* Products that took the large tiles, of those that the calling thread has
  * enqueued so far.  Host-only. */

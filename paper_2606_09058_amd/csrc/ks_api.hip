@@ -8,6 +8,7 @@
 
 #include <new>
 
+#include "../../include/ks_testing.h"
 #include "ks_internal.hpp"
 
 using namespace ks;
@@ -1205,6 +1206,16 @@ ks_status ks_plan_get_graph_stats(ks_plan* p, int64_t* captures, int64_t* replay
     if (!p || !captures || !replays) return KS_ERR_INVALID_ARG;
     *captures = p->graph_captures;
     *replays = p->graph_replays;
+    return KS_OK;
+}
+
+int32_t ks_test_graph_forks(ks_plan* p, int32_t* forks) {
+    if (!p || !forks || !p->graph) return KS_ERR_INVALID_ARG;
+    size_t nodes = 0, edges = 0;
+    if (hipGraphGetNodes(p->graph, nullptr, &nodes) != hipSuccess ||
+        hipGraphGetEdges(p->graph, nullptr, nullptr, &edges) != hipSuccess)
+        return KS_ERR_HIP;
+    *forks = (int32_t)((long)edges - ((long)nodes - 1));
     return KS_OK;
 }
 
