@@ -218,13 +218,16 @@ __device__ inline double fermi_count(double x, double none) {
 // chunks of 64, of which only those near the point are looked at: a chunk 40 kT below
 // it is full, and one beyond `none` = 44 + ln(states / electrons) is empty (all
 // such states together hold less than 1e-19 of the electrons asked for, however few
-// these are).  A lane keeps what a wavefront has to know of one of its chunks.  Up to 12 chunks
-// every wavefront has them all, and the sixteen count at the 15 inner points
+// these are).  A lane keeps what a wavefront has to know of one of its chunks.
+// Few chunks: every wavefront has them all, and the sixteen count at the 15 inner points
 // of four halvings at once; beyond, the wavefronts share the chunks of one count.
 // (Against all eigenvalues at every halving: order 64 76 -> 21 us, 8 x 208
-// 230 -> 97, 1300 106 -> 50, 16 x 1300 800 -> 158.  The line at 12 chunks: with 21
-// and 32 of them in every wavefront 70 and 108 us, shared 50 and 97.)
-constexpr int FERMI_CHUNKS = 64, FERMI_FEW = 12;  // chunks in LDS, chunks in every wavefront
+// 230 -> 97, 1300 106 -> 50, 16 x 1300 800 -> 158.  The line, whole density builds in us, all chunks in
+// every wavefront against shared: orders 448 and 512 60.0, 61.5 and 62.7, 62.5; of a
+// batch, whose k-points each have a chunk near the level, 3 and 5 of order 64 51.8, 57.4
+// and 68.0, 64.2.)
+constexpr int FERMI_CHUNKS = 64;                   // chunks in LDS
+constexpr int FERMI_FEW = 7, FERMI_FEW_BATCH = 4;  // chunks in every wavefront
 __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const double* eps,
                                                      KWeights kw, double g, double ne, double kT,
                                                      int il, int iu, double* occ, double* mu_out,
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(1024) void fermi_kernel(int batch, int order, const
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int per = (order + 63) / 64;  // chunks of a k-point
     const long nchunk = (long)batch * per;
-    const bool few = nchunk <= FERMI_FEW, lds = nchunk <= FERMI_CHUNKS, held = nchunk <= 16 * 64;
+    const bool few = nchunk <= (batch == 1 ? FERMI_FEW : FERMI_FEW_BATCH), lds = nchunk <= FERMI_CHUNKS, held = nchunk <= 16 * 64;
     // chunk c of the wavefront: c itself, or c * 16 + wave
     auto chunk_id = [&](long c) { return few ? c : c * 16 + wave; };
     double mn = INFINITY, mx = -INFINITY;

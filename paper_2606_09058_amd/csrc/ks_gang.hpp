@@ -98,6 +98,14 @@ __device__ __forceinline__ double mk_<double>(double re, double) { return re; }
 template <>
 __device__ __forceinline__ cplx mk_<cplx>(double re, double im) { return mk(re, im); }
 
+// acc += a b, a fused multiply-add per real product
+__device__ __forceinline__ void fma_(double& acc, double a, double b) { acc = fma(a, b, acc); }
+__device__ __forceinline__ void fma_(cplx& acc, cplx a, cplx b) {
+    acc.x = fma(-a.y, b.y, fma(a.x, b.x, acc.x));
+    acc.y = fma(a.y, b.x, fma(a.x, b.y, acc.y));
+}
+
+
 // H_k = I - tau v v^H from alpha = x_{k+1} and |x_{k+2..}|^2 (as in ks_hetrd.hip).
 template <typename T>
 __device__ __forceinline__ void form_reflector(T alpha, double xn2, T& sc, T& tv, double& beta) {
@@ -107,17 +115,10 @@ __device__ __forceinline__ void form_reflector(T alpha, double xn2, T& sc, T& tv
         beta = ar;
         sc = zero_<T>();
     } else {
-        beta = -copysign(sqrt(ar * ar + ai * ai + xn2), ar);
+        beta = -copysign(sqrt(fma(ar, ar, fma(ai, ai, xn2))), ar);
         tv = mk_<T>((beta - ar) / beta, -ai / beta);
         sc = inv_(alpha - from_re<T>(beta));
     }
-}
-
-// acc += a b, a fused multiply-add per real product
-__device__ __forceinline__ void fma_(double& acc, double a, double b) { acc = fma(a, b, acc); }
-__device__ __forceinline__ void fma_(cplx& acc, cplx a, cplx b) {
-    acc.x = fma(-a.y, b.y, fma(a.x, b.x, acc.x));
-    acc.y = fma(a.y, b.x, fma(a.x, b.y, acc.y));
 }
 
 __device__ __forceinline__ double mul_(double a, double b) { return a * b; }

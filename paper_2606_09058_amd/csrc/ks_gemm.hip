@@ -708,7 +708,17 @@ __global__ __launch_bounds__(256) void gemm_thin_kernel(int m, int n, int K, dou
 // FP64 products that take the thin kernel: fewer 64 x 64 tiles than THIN_TILES, one
 // per compute unit (beyond, the larger tiles' reuse is worth more than the split).
 constexpr long THIN_TILES = 256;
-constexpr int THIN_SPLITK = 640;  // largest inner dimension at which they replace a split-K product
+// They replace a split-K product of the back-transform up to these inner dimensions,
+// for complex data only with few tiles: whole back-transforms by blocks of 128 (us, split-K
+// against thin) 760 real 274, 257, 900 real 362 both, 1100 494, 501; 600 complex 453
+// both, 680 508, 522; four complex matrices of 400 (56 tiles) 493, 444, of 520 (72 tiles) 735, 820.
+template <typename T>
+constexpr int THIN_SPLITK = std::is_same<T, cplx>::value ? 640 : 800;
+constexpr long THIN_SPLITK_TILES = 64;
+template <typename T>
+static bool thin_splitk(int k, long tiles) {
+    return k <= THIN_SPLITK<T> && (!std::is_same<T, cplx>::value || tiles <= THIN_SPLITK_TILES);
+}
 template <typename T>
 static bool thin(int m, int n, int batch, Uplo uplo) {
     if (!std::is_same<T, double>::value && !std::is_same<T, cplx>::value) return false;
@@ -813,16 +823,15 @@ void gemm_splitk(hipStream_t s, Op opa, Op opb, int m, int n, int k, double alph
                  const T* B, int ldb, double beta, T* C, int ldc, T* work, long work_elems, int batch, long sa,
                  long sb, long sc) {
     if (m <= 0 || n <= 0 || batch <= 0) return;
-    // the chunking depends on one matrix's shape only, so a batched product
-    // rounds exactly like the same product on its own
+    // the chunking depends on one matrix's shape only, so a batched product rounds
+    // like the same product on its own (as long as both are thin or neither is)
     long tiles = (long)cdiv(m, BM) * cdiv(n, BN);
     int nz = (int)std::max<long>(1, std::min<long>(cdiv(1024, tiles), cdiv(k, 256)));
     while (nz > 1 && (long)nz * m * n * batch > work_elems) --nz;
     int kc = ((cdiv(k, nz) + BK - 1) / BK) * BK;
     nz = cdiv(k, kc);
-    // (short inner dimensions fit the thin kernel's four wavefronts: 26 us against
-    // 37 for 128 x 520 x 520 complex, but 67 against 45 for 128 x 1300 x 1300)
-    if (nz <= 1 || k <= 0 || (k <= THIN_SPLITK && thin<T>(m, n, batch, UPLO_FULL))) {
+    // (short inner dimensions fit the thin kernel's four wavefronts)
+    if (nz <= 1 || k <= 0 || (thin_splitk<T>(k, tiles * batch) && thin<T>(m, n, batch, UPLO_FULL))) {
         gemm<T>(s, opa, opb, m, n, k, alpha, A, lda, sa, B, ldb, sb, beta, C, ldc, sc, batch);
         return;
     }

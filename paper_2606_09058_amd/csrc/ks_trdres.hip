@@ -132,7 +132,8 @@ __global__ __launch_bounds__(64 * NW) void trd_wave_kernel(int n, int k0, const 
         T sc, tv;
         double beta;
         form_reflector<T>(alpha, xn2, sc, tv, beta);
-        const T c1 = from_re<T>(1.0) - sc * alpha;
+        T c1 = from_re<T>(1.0);
+        fma_(c1, -sc, alpha);
         T* zb = zbuf[k & 1];
         T* rb = rbuf[k & 1];
         const int r1 = k1 / NW;  // slot of the raw row, on wavefront k1 % NW
@@ -190,9 +191,12 @@ __global__ __launch_bounds__(64 * NW) void trd_wave_kernel(int n, int k0, const 
                 if (in) V[(long)j * n + k] = v[c];
             }
         }
-        const T p1 = sc * zb[(k1 % NW) * R + k1 / NW] + c1 * conj_(rb[k1]);
+        T p1 = mul_(c1, conj_(rb[k1]));
+        fma_(p1, sc, zb[(k1 % NW) * R + k1 / NW]);
         const double alw = -0.5 * abs2_(tv) * lane_sum(gs);
-        const T w1 = conj_(tv * p1 + from_re<T>(alw));
+        T w1 = from_re<T>(alw);
+        fma_(w1, tv, p1);
+        w1 = conj_(w1);
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int j = lane + 64 * c;
@@ -405,7 +409,8 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
         T sc, tv;
         double beta;
         form_reflector<T>(alpha, xn2, sc, tv, beta);
-        const T c1 = from_re<T>(1.0) - sc * alpha;
+        T c1 = from_re<T>(1.0);
+        fma_(c1, -sc, alpha);
         T v[C], p[C], row[C], vo = zero_<T>(), po = vo;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -510,7 +515,9 @@ __global__ __launch_bounds__(NT, WPE) void trd_gang_kernel(int n, int k0, int ke
 #pragma unroll
         for (int q = 0; q < NW; ++q) gr += red2[q];
         const double alw = -0.5 * abs2_(tv) * gr;
-        const T w1 = conj_(tv * sp1 + from_re<T>(alw));
+        T w1 = from_re<T>(alw);
+        fma_(w1, tv, sp1);
+        w1 = conj_(w1);
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int j = jc[c];
@@ -842,9 +849,10 @@ long gang_mem(int order, int batch) {
 }
 
 // Columns k0 .. n-1: a gang hands over to a smaller shape where that takes at
-// least a fifth less per column (a hand-over costs three launches and two
-// passes over the rest, about 30 us), and the last columns to one
-// workgroup.
+// least a tenth less per column (a hand-over costs three launches and two
+// passes over the rest), and the last columns to one workgroup.  (Whole tridiagonalisations, us,
+// with the line at 0.7, 0.8, 0.9 and 1: 520 real 1224, 1223, 1143, 1114; 2600 real 8299,
+// 7662, 7484, 7496; 1300 complex 4921, 4902, 4802, 5002; 2048 complex 12021, 11160, 11057, 11520.)
 template <typename T, typename S>
 void hetrd_resident(hipStream_t s, int n, int k0, S* A, int lda, long sA, int B, double* d, double* e, T* tau, T* Vall,
                     GangWork<T> gw, int* info) {
@@ -856,7 +864,7 @@ void hetrd_resident(hipStream_t s, int n, int k0, S* A, int lda, long sA, int B,
         int next = std::max(last, 1 << g[p].lp);
         for (int i = 0; i < ns; ++i) {
             const int q = g[i].order < m ? pick_shape<T>(g[i].order, B, gw.ncu, gw.mem != nullptr) : -1;
-            if (q >= 0 && gang_us(g[q], B, gw.ncu) <= 0.8 * gang_us(g[p], B, gw.ncu)) next = std::max(next, g[i].order);
+            if (q >= 0 && gang_us(g[q], B, gw.ncu) <= 0.9 * gang_us(g[p], B, gw.ncu)) next = std::max(next, g[i].order);
         }
         const int kend = m - std::min(next, m - 1);
         // gangs that take the whole chip: one matrix's launches behind the other's, so
