@@ -706,8 +706,32 @@ __global__ __launch_bounds__(256) void gemm_thin_kernel(int m, int n, int K, dou
 }
 
 // FP64 products that take the thin kernel: fewer 64 x 64 tiles than THIN_TILES, one
-// per compute unit (beyond, the larger tiles' reuse is worth more than the split).
+// per compute unit (beyond, the larger tiles' reuse is worth more than the split),
+// and with an inner dimension above THIN_K no more 32 x 32 tiles than THIN_WGS: there
+// the four wavefronts have work enough, and twice the operand bytes per product decide.
+// (Triangular operands cut the inner dimension differently for every tile, which the
+// small ones even out: order 1000 reduction real 146 -> 103 us, complex 331 -> 233.)
+// Whole calls (us, 64 x 64 tiles against thin) on both sides of the lines: the lower
+// triangle of C w C^H (energy density) real 900 97, 73, 1000 105, 131, complex 900 194, 180,
+// 1000 204, 278; six full products (backward) real 700 322, 243, 800 367, 403, complex 800 826,
+// 738, 900 945, 1080; the lower triangle of V^H (H V) (Loewdin reduction) complex 800 271,
+// 252, 900 311, 345, real ones up to the tiles' line (1300 277, 233).
 constexpr long THIN_TILES = 256;
+constexpr int THIN_K = 256;
+template <typename T, int OPA>
+constexpr long thin_wgs(bool lower) {
+    if (std::is_same<T, cplx>::value) return !lower ? 640 : OPA == OP_N ? 450 : 350;
+    return !lower ? 512 : OPA == OP_N ? 450 : 4 * THIN_TILES;
+}
+template <typename T, int OPA>
+static bool thin(int m, int n, int k, int batch, Uplo uplo, Tri tri) {
+    if (!std::is_same<T, double>::value && !std::is_same<T, cplx>::value) return false;
+    const int half = uplo != UPLO_FULL ? 2 : 1;
+    if ((long)cdiv(m, BM) * cdiv(n, BN) * batch / half >= THIN_TILES) return false;
+    return k <= THIN_K || tri != TRI_NONE ||
+           (long)cdiv(m, 32) * cdiv(n, 32) * batch / half <= thin_wgs<T, OPA>(half == 2);
+}
+
 // They replace a split-K product of the back-transform up to these inner dimensions,
 // for complex data only with few tiles: whole back-transforms by blocks of 128 (us, split-K
 // against thin) 760 real 274, 257, 900 real 362 both, 1100 494, 501; 600 complex 453
@@ -719,12 +743,6 @@ template <typename T>
 static bool thin_splitk(int k, long tiles) {
     return k <= THIN_SPLITK<T> && (!std::is_same<T, cplx>::value || tiles <= THIN_SPLITK_TILES);
 }
-template <typename T>
-static bool thin(int m, int n, int batch, Uplo uplo) {
-    if (!std::is_same<T, double>::value && !std::is_same<T, cplx>::value) return false;
-    return (long)cdiv(m, BM) * cdiv(n, BN) * batch / (uplo != UPLO_FULL ? 2 : 1) < THIN_TILES;
-}
-
 template <typename T, int OPA, int OPB>
 static void launch(hipStream_t s, int m, int n, int k, double alpha, const T* A, int lda, long sa,
                    const T* B, int ldb, long sb, double beta, T* C, int ldc, long sc, int batch,
@@ -741,7 +759,7 @@ static void launch(hipStream_t s, int m, int n, int k, double alpha, const T* A,
         return;
     }
     if constexpr (std::is_same<T, double>::value || std::is_same<T, cplx>::value) {
-        if (thin<T>(m, n, batch, uplo)) {
+        if (thin<T, OPA>(m, n, k, batch, uplo, tri)) {
             dim3 grid(cdiv(n, 32), cdiv(m, 32), batch);
             hipLaunchKernelGGL((gemm_thin_kernel<T, OPA, OPB>), grid, dim3(256), 0, s, m, n, k, alpha, A, lda, sa, B,
                                ldb, sb, beta, C, ldc, sc, kscale, sk, (int)uplo, kdev, (int)tri);
@@ -831,7 +849,7 @@ void gemm_splitk(hipStream_t s, Op opa, Op opb, int m, int n, int k, double alph
     int kc = ((cdiv(k, nz) + BK - 1) / BK) * BK;
     nz = cdiv(k, kc);
     // (short inner dimensions fit the thin kernel's four wavefronts)
-    if (nz <= 1 || k <= 0 || (thin_splitk<T>(k, tiles * batch) && thin<T>(m, n, batch, UPLO_FULL))) {
+    if (nz <= 1 || k <= 0 || (thin_splitk<T>(k, tiles * batch) && thin<T, OP_C>(m, n, k, batch, UPLO_FULL, TRI_NONE))) {
         gemm<T>(s, opa, opb, m, n, k, alpha, A, lda, sa, B, ldb, sb, beta, C, ldc, sc, batch);
         return;
     }
