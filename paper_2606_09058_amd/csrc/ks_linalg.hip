@@ -111,6 +111,10 @@ __device__ __forceinline__ double rsqrt_(double d) {
 // pivots: 22 to 23 us against 36 to 41 for the kernel above.  (Complex columns, with four lane
 // broadcasts for each entry, took 55 this way against 43.)
 constexpr int LS = 16;  // columns of a panel
+// Up to this order the columns of the kernel above are the shorter chain (the whole
+// factorisation, us, columns against panels: order 4 11.5, 25.5, 16 18.6, 25.5, 28 25.0, 27.7,
+// 8 matrices of 28 and 32 27.6, 28.2 and 30.2, 28.2).
+constexpr int PANELS_FROM = 28;
 __global__ __launch_bounds__(CB / LS * 64) void potrf_inv_panels_kernel(int nb, double* A, int lda, long sa, double* D,
                                                                       int ldd, long sd, int col0, int* info) {
     __shared__ double sL[CB][CB + 1];
@@ -226,10 +230,10 @@ template <typename T>
 static void potrf_inv_rec(hipStream_t s, int n, T* L, int ldl, long sl, T* Li, int ldi, long si, T* Tw, long st,
                           int batch, int col0, int* info) {
     if (n <= CB) {
-        if constexpr (is_cplx<T>::value)
+        if (is_cplx<T>::value || n <= PANELS_FROM)
             hipLaunchKernelGGL((potrf_inv_leaf_kernel<T>), dim3(batch), dim3(64 * LW), 0, s, n, L, ldl, sl, Li, ldi, si,
                                col0, info);
-        else
+        else if constexpr (!is_cplx<T>::value)
             hipLaunchKernelGGL(potrf_inv_panels_kernel, dim3(batch), dim3(CB / LS * 64), 0, s, n, L, ldl, sl, Li, ldi,
                                si, col0, info);
         return;
