@@ -72,11 +72,11 @@ def nominal_flops(order, ncols, m_occ, cplx, n_s):
 
 
 def measured_traffic(workload):
-    """Per-launch memory traffic of symv_kernel from the committed counter summary
-    (profiles/symv_kernel_<workload>_traffic.txt: FETCH_SIZE + WRITE_SIZE runs,
+    """Per-launch memory traffic of trd_panel_kernel from the committed counter summary
+    (profiles/trd_panel_kernel_<workload>_traffic.txt: FETCH_SIZE + WRITE_SIZE runs,
     each scaled by a plain copy of known size), or None if there is none for
     this workload or the kernel source has changed since it was taken."""
-    path = os.path.join(ROOT, "profiles", "symv_kernel_%s_traffic.txt" % workload)
+    path = os.path.join(ROOT, "profiles", "trd_panel_kernel_%s_traffic.txt" % workload)
     if not os.path.exists(path):
         return None
     kv = {}
@@ -239,13 +239,18 @@ def time_route(p, H, S, route, steps, warmup, stride, stream, graph=False, warm=
 
 
 def symv_roofline(prof, traffic):
+    """The sampled launches against the memory's rate.  A panel keeps a part of its triangle on
+    the chip, so where its traffic has been measured, achieved and frac are of that, and the rate
+    of the algorithmic bytes (the triangle once per column) stands beside them."""
     hemv_avg_us = 1e3 * prof.hemv_ms / max(1, prof.hemv_launches)
     hemv_gbs = prof.hemv_bytes / max(1e-12, prof.hemv_ms * 1e-3) / 1e9
+    gbs = hemv_gbs * (traffic["over_algorithmic"] if traffic else 1.0)
     return {"bound": "hbm", "kernel": "trailing Hermitian matrix-vector products of the one-stage tridiagonalisation "
                                       "(a sampled launch is a panel of 32 columns, trd_panel_kernel, for one matrix; "
-                                      "a column's symv_kernel for a batch); bytes: the lower triangle once per column, "
-                                      "of which a panel keeps a part on the chip",
-            "achieved": hemv_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": hemv_gbs / PEAK_HBM_GBS,
+                                      "a column's symv_kernel for a batch)",
+            "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS,
+            "bytes": "measured traffic" if traffic else "algorithmic: the lower triangle once per column",
+            "algorithmic_gbs": hemv_gbs,
             "traffic": traffic["bytes"] if traffic else None,
             "traffic_over_algorithmic": traffic["over_algorithmic"] if traffic else None,
             "traffic_source": traffic["source"] if traffic else None,
