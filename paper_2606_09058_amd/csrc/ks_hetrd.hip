@@ -755,9 +755,8 @@ struct TrdGroup {
 // else, reflectors included, stays in FP64).
 // A batch of two or more matrices with a side stream in the workspace runs as
 // two groups, the second half on the side stream (forked from and joined back
-// to s by events; both on s while that is captured), their launches issued column by
-// column in turn: one group's latency-bound column kernel then runs beside the other
-// group's product.
+// to s by events), their launches issued column by column in turn: one group's
+// latency-bound column kernel then runs beside the other group's product.
 template <typename T, typename S>
 void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, double* e, T* tau, T* Vall,
            HetrdWork<T>& w) {
@@ -770,9 +769,11 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
     GangWork<T> gang = w.gang;
     bool fork = false;
     if (w.side && batch >= 2 && n > mres) {
-        // A captured sequence keeps both groups on the plan's stream: replays of a
-        // forked one ran their launches one after the other all the same (16 x 1300:
-        // 0.0676 s against 0.0625 eager), and one ended the process.
+        // A captured sequence is a chain (one that forked ended the process after many
+        // replays): its columns take the whole batch in one launch, which the halves of
+        // a batch in turn on one stream do not reach (16 x 1300: 50.5 against 53.3 ms
+        // a batch, 47.3 eager), and the rank-2NB updates stay by halves, so that they
+        // take the same kernels as eager ones.
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
         fork = cap == hipStreamCaptureStatusNone;
@@ -798,6 +799,11 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
             (void)hipStreamWaitEvent(w.side, w.fork, 0);
         }
     }
+    // the groups of the column kernels
+    const bool whole = ng == 2 && !fork;
+    TrdGroup<T, S> all[1] = {{s, batch, A, d, e, tau, Vall, w}};
+    TrdGroup<T, S>* cg = whole ? all : g;
+    const int nc = whole ? 1 : ng;
     int k0 = 0;
     for (; n - k0 > mres; k0 += nb) {
         int jb = min(nb, n - 1 - k0);
@@ -820,8 +826,8 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
                 w.prof->push(PROF_HEMV, e0, e1, bytes);
             }
         }
-        for (int q = 0; q < ng && !panel; ++q) {
-            TrdGroup<T, S>& G = g[q];
+        for (int q = 0; q < nc && !panel; ++q) {
+            TrdGroup<T, S>& G = cg[q];
             // The column kernels write every panel row the trailing update and
             // the next columns read (rows k+1.. of column k); only a short last
             // panel leaves panel columns unwritten that its update would read.
@@ -843,10 +849,10 @@ void hetrd(hipStream_t s, int n, S* A, int lda, long sA, int batch, double* d, d
             const bool smp = w.prof && w.prof->sample();
             hipEvent_t e0 = smp ? w.prof->take() : nullptr;
             hipEvent_t e1 = smp ? w.prof->take() : nullptr;
-            for (int q = 0; q < ng; ++q) {
-                TrdGroup<T, S>& G = g[q];
+            for (int q = 0; q < nc; ++q) {
+                TrdGroup<T, S>& G = cg[q];
                 symv_launch<T, S>(G.s, sch, n, k, j, G.A, lda, sA, G.B, nA, G.w, q == 0 ? e0 : nullptr,
-                                  q == ng - 1 ? e1 : nullptr);
+                                  q == nc - 1 ? e1 : nullptr);
                 hipLaunchKernelGGL((wcol_kernel<T, S>), dim3(nt, 1, G.B), dim3(64 * Wc<T>::NW), 0, G.s, n, k, j, nb,
                                    (int)(j + 1 < jb), G.A, lda, sA, nt, nch, sch, nA, G.d, G.e, G.tau, G.w);
             }
