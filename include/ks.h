@@ -78,15 +78,18 @@ enum { KS_FP64 = 0, KS_MIXED = 1 };                  /* arithmetic of the solve 
 /* Plan flags.  KS_PLAN_GRAPH: ks_gevd captures its launch sequence from the
  * plan stream into a HIP graph the first time it sees an argument set (H, S,
  * eps, C, il, iu, flags) and replays the graph while the same set repeats; a
- * different set is captured afresh.  Needs a non-NULL stream.  The batched
- * launches (all k-points of the plan in each kernel) are the same either way,
- * so results do not depend on the flag. */
+ * different set is captured afresh.  Needs a non-NULL stream.  A captured
+ * sequence is a chain on that one stream; the sums are formed in the same
+ * order either way, so results do not depend on the flag. */
 enum { KS_PLAN_GRAPH = 1u,
        /* KS_PLAN_AUTOTUNE: at ks_plan_create, time the candidate tile shapes of
         * the tridiagonalisation's symmetric product (tiles per workgroup) on the
         * plan's own order and batch, and keep the fastest (synchronous, a few
         * milliseconds; without the flag a fixed default is used).  The choice
-        * changes only the grouping of partial sums, not the algorithm. */
+        * changes only the grouping of partial sums, not the algorithm.  It is
+        * used where that product runs: batches beyond the orders whose columns
+        * stay on the chip, and single matrices beyond order 11132 or where
+        * compute units are masked off. */
        KS_PLAN_AUTOTUNE = 2u,
        /* KS_PLAN_LOWDIN: ks_gevd takes the paper's own route (Sec. 3.1 Parts
         * 2-1..2-5, Sec. 3.2 Parts 3-1..3-6) instead of the Cholesky one:
@@ -140,8 +143,10 @@ typedef struct ks_plan ks_plan; /* opaque: workspace, cached Cholesky factor, in
 typedef struct {
     int32_t n;          /* orbitals per spin block; order = n (collinear) or 2n   */
     int32_t batch;      /* k-points solved together (>= 1, <= 64): every kernel of  */
-                        /* the solve takes all of them in one launch, except the   */
-                        /* tridiagonalisation (two halves on two streams)          */
+                        /* the solve takes all of them in one launch, except in    */
+                        /* the tridiagonalisation, where columns beyond the orders */
+                        /* kept on the chip run as two halves on two streams, and  */
+                        /* matrices that need the whole chip run one by one        */
     int32_t dtype;      /* KS_REAL64 or KS_COMPLEX128; noncollinear needs complex  */
     int32_t spin;       /* KS_COLLINEAR (g = 2) or KS_NONCOLLINEAR (g = 1)         */
     int32_t precision;  /* KS_FP64 or KS_MIXED (FP32 trailing updates, refined)    */
@@ -157,9 +162,10 @@ typedef struct {
  * KS_ERR_ALLOC if the workspace does not fit.  On success *out owns the
  * workspace until ks_plan_destroy.  A plan for a batch of two or more also
  * owns a side stream (non-blocking, default priority) and two events: the
- * tridiagonalisation runs half of the batch there, forked from and joined
- * back to the plan's stream within each ks_gevd call, so callers order work
- * on the plan's stream alone (KS_ERR_HIP if they cannot be created). */
+ * tridiagonalisation's columns of large matrices run half of the batch there,
+ * forked from and joined back to the plan's stream within each ks_gevd call
+ * (not under capture), so callers order work on the plan's stream alone
+ * (KS_ERR_HIP if they cannot be created). */
 ks_status ks_plan_create(const ks_plan_desc* desc, ks_plan** out);
 
 /* Free the plan's workspace, side stream and events (synchronizes its streams

@@ -8,7 +8,7 @@
 // Measured, whole tridiagonalisation: order 64 real 0.70 -> 0.07 ms, 333 real
 // 4.0 -> 0.68, 520 complex 9.1 -> 1.6, 1024 real 13.1 -> 2.4, 1300 complex
 // 24.4 -> 5.0, 2048 complex 40.5 -> 11.0, 2600 real 36.7 -> 7.7, 16 x 1300
-// complex 41.7 -> 27.5 ms.
+// complex 41.7 -> 24.6 ms.
 //
 // A gang of workgroups owns the full rows of the trailing matrix cyclically
 // (local row i on workgroup i mod P, slot i / P), a thread C columns of them.
